@@ -784,28 +784,20 @@ fp_status fp_metrics(const fp_grid* g, int32_t Y, const double* xyz, double* met
             cnt[d] = g->n[d] + 2 * g->ghost;
         }
     }
-    const long tot = (long)cnt[0] * cnt[1] * cnt[2];
-    const unsigned blocks = (unsigned)((tot + 127) / 128);
-#define FP_MET_LAUNCH(D, YY) \
-    hipLaunchKernelGGL((k_metrics<D, YY>), dim3(blocks), dim3(128), 0, s, G, C, xyz, met, lo[0], lo[1], lo[2], cnt[0], cnt[1], cnt[2])
-    if (g->ndim == 3) {
-        switch (Y) {
-        case 2: FP_MET_LAUNCH(3, 2); break;
-        case 4: FP_MET_LAUNCH(3, 4); break;
-        case 6: FP_MET_LAUNCH(3, 6); break;
-        default: FP_MET_LAUNCH(3, 8); break;
-        }
-    } else {
-        switch (Y) {
-        case 2: FP_MET_LAUNCH(2, 2); break;
-        case 4: FP_MET_LAUNCH(2, 4); break;
-        case 6: FP_MET_LAUNCH(2, 6); break;
-        default: FP_MET_LAUNCH(2, 8); break;
-        }
+#define FP_MET_LAUNCH(YY)                                                                                         \
+    if (g->ndim == 3)                                                                                             \
+        hipLaunchKernelGGL(k_metrics3<YY>, dim3((unsigned)met_tiles<YY>(cnt)), dim3(MetTile<YY>::THREADS), 0, s,  \
+                           G, C, xyz, met, lo[0], lo[1], lo[2], cnt[0], cnt[1], cnt[2]);                          \
+    else                                                                                                          \
+        hipLaunchKernelGGL(k_metrics2<YY>, dim3((unsigned)(((long)cnt[0] * cnt[1] + 127) / 128)), dim3(128), 0,   \
+                           s, G, C, xyz, met, lo[0], lo[1], cnt[0], cnt[1])
+    switch (Y) {
+    case 2: FP_MET_LAUNCH(2); break;
+    case 4: FP_MET_LAUNCH(4); break;
+    case 6: FP_MET_LAUNCH(6); break;
+    default: FP_MET_LAUNCH(8); break;
     }
 #undef FP_MET_LAUNCH
-    hipLaunchKernelGGL(k_periodic_fill, dim3((unsigned)((G.vol + 255) / 256)), dim3(256), 0, s, G,
-                       g->ndim, g->ndim == 3 ? 10 : 5, met);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "fp_metrics launch");
     return FP_OK;

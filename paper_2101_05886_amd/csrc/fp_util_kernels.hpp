@@ -5,6 +5,14 @@
 
 namespace fpk {
 
+// XCD-aware workgroup order: the dispatcher hands workgroups to the 8 XCDs
+// round-robin (b -> XCD b mod 8), each XCD with its own L2.  Renumbering
+// gives XCD x a contiguous range of the work instead of every eighth item.
+__device__ __forceinline__ long xcd_block(long b, long nb) {
+    const long per = nb / 8, rem = nb % 8, x = b % 8;
+    return x * per + (x < rem ? x : rem) + b / 8;
+}
+
 // ---------------------------------------------------------------------------
 // symmetric conservative metrics (setup)
 // ---------------------------------------------------------------------------
@@ -44,98 +52,176 @@ struct Coord {
             s += dcoef<Y>(m) * (X(c, off + m * C.csd[e]) - X(c, off - m * C.csd[e]));
         return s;
     }
-    // P_e = a_e b - a b_e (the pairing of eq. JBabc)
-    __device__ __forceinline__ double P(int a, int b, int e, long off) const {
-        return D(a, e, off) * X(b, off) - X(a, off) * D(b, e, off);
-    }
-    // s_{d,c}: with (e, f) = (d+1, d+2) and (a, b) = (c+1, c+2) cyclically,
-    // s_{d,c} = 1/2 [ (a_e b - a b_e)_f - (a_f b - a b_f)_e ]
-    __device__ __forceinline__ double s3(int d, int c, long off) const {
-        const int e = (d + 1) % 3, f = (d + 2) % 3;
-        const int a = (c + 1) % 3, b = (c + 2) % 3;
-        double sf = 0.0, se = 0.0;
-#pragma unroll
-        for (int m = 1; m <= Y / 2; ++m) {
-            sf += dcoef<Y>(m) * (P(a, b, e, off + m * C.csd[f]) - P(a, b, e, off - m * C.csd[f]));
-            se += dcoef<Y>(m) * (P(a, b, f, off + m * C.csd[e]) - P(a, b, f, off - m * C.csd[e]));
-        }
-        return 0.5 * (sf - se);
-    }
-    // x . s_d at a node (the flux of eq. JB)
-    __device__ __forceinline__ double xs3(int d, long off) const {
-        return X(0, off) * s3(d, 0, off) + X(1, off) * s3(d, 1, off) + X(2, off) * s3(d, 2, off);
-    }
 };
 
-template <int DIM, int Y>
-__global__ __launch_bounds__(128) void k_metrics(GeoK G, CGeoK C, const double* __restrict__ xyz,
-                                                  double* met, int lo0, int lo1, int lo2, int c0,
-                                                  int c1, int c2) {
-    const long tid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (tid >= (long)c0 * c1 * c2) return;
-    const int i = lo0 + (int)(tid % c0);
-    const int j = lo1 + (int)((tid / c0) % c1);
-    const int k = lo2 + (int)(tid / ((long)c0 * c1));
-    const Coord<Y> X{xyz, C};
-    const long co = C.cbase + i + j * C.csd[1] + (long)k * C.csd[2];
-    const long mo = G.base + i + j * G.sd[1] + (long)k * G.sd[2];
-    if constexpr (DIM == 3) {
-#pragma unroll 1
-        for (int d = 0; d < 3; ++d)
-#pragma unroll 1
-            for (int c = 0; c < 3; ++c) met[(3 * d + c) * G.vol + mo] = X.s3(d, c, co);
-        double J = 0.0;
-#pragma unroll 1
-        for (int d = 0; d < 3; ++d) {
-            double s = 0.0;
-#pragma unroll 1
-            for (int m = 1; m <= Y / 2; ++m)
-                s += dcoef<Y>(m) * (X.xs3(d, co + m * C.csd[d]) - X.xs3(d, co - m * C.csd[d]));
-            J += s;
-        }
-        met[9 * G.vol + mo] = J / 3.0;
-    } else {
-        met[0 * G.vol + mo] = X.D(1, 1, co);
-        met[1 * G.vol + mo] = -X.D(0, 1, co);
-        met[2 * G.vol + mo] = -X.D(1, 0, co);
-        met[3 * G.vol + mo] = X.D(0, 0, co);
-        // 1/J = 1/2 [ (x y_eta - y x_eta)_xi + (y x_xi - x y_xi)_eta ]
-        double a = 0.0, b = 0.0;
+// Stores one computed node's metric v at (i, j, k) and at its periodic
+// images in the ghost layers (every array of the layout is then complete:
+// no fill pass).  A node within g of an end of a periodic axis has an image
+// beyond the other end; an axis of fewer than 2 g nodes gives both.
+template <int DIM>
+__device__ __forceinline__ void met_store(const GeoK& G, double* __restrict__ a, int i, int j, int k, double x) {
+    a[G.base + i + j * G.sd[1] + k * G.sd[2]] = x;
+    const int p[3] = {i, j, k};
+    bool edge = false;
 #pragma unroll
-        for (int m = 1; m <= Y / 2; ++m) {
-            const long p = co + m * C.csd[0], q = co - m * C.csd[0];
-            a += dcoef<Y>(m) * ((X.X(0, p) * X.D(1, 1, p) - X.X(1, p) * X.D(0, 1, p)) -
-                                (X.X(0, q) * X.D(1, 1, q) - X.X(1, q) * X.D(0, 1, q)));
-            const long r = co + m * C.csd[1], s = co - m * C.csd[1];
-            b += dcoef<Y>(m) * ((X.X(1, r) * X.D(0, 0, r) - X.X(0, r) * X.D(1, 0, r)) -
-                                (X.X(1, s) * X.D(0, 0, s) - X.X(0, s) * X.D(1, 0, s)));
-        }
-        met[4 * G.vol + mo] = 0.5 * (a + b);
+    for (int d = 0; d < DIM; ++d) edge = edge || (G.bc[d] == 0 && (p[d] < G.g || p[d] >= G.n[d] - G.g));
+    if (!edge) return;
+    int lo[3], hi[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const bool per = d < DIM && G.bc[d] == 0;
+        lo[d] = per && p[d] >= G.n[d] - G.g ? -1 : 0;
+        hi[d] = per && p[d] < G.g ? 1 : 0;
     }
+    for (int c = lo[2]; c <= hi[2]; ++c)
+        for (int b = lo[1]; b <= hi[1]; ++b)
+            for (int e = lo[0]; e <= hi[0]; ++e)
+                a[G.base + (i + e * G.n[0]) + (j + b * G.n[1]) * G.sd[1] + (k + c * G.n[2]) * G.sd[2]] = x;
 }
 
-// Periodic ghost layers of any [nvar][...] array: copy from the image.
-__global__ __launch_bounds__(256) void k_periodic_fill(GeoK G, int ndim, int nvar, double* a) {
+// 2D metrics, one lane per node.
+template <int Y>
+__global__ __launch_bounds__(128) void k_metrics2(GeoK G, CGeoK C, const double* __restrict__ xyz,
+                                                  double* __restrict__ met, int lo0, int lo1, int c0, int c1) {
     const long tid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (tid >= G.vol) return;
-    int N[3];
-    N[0] = G.n[0] + 2 * G.g;
-    N[1] = G.n[1] + 2 * G.g;
-    N[2] = ndim == 3 ? G.n[2] + 2 * G.g : 1;
-    int p[3];
-    p[0] = (int)(tid % N[0]) - G.g;
-    p[1] = (int)((tid / N[0]) % N[1]) - G.g;
-    p[2] = ndim == 3 ? (int)(tid / ((long)N[0] * N[1])) - G.g : 0;
-    bool moved = false;
-    for (int d = 0; d < ndim; ++d) {
-        if (G.bc[d] == 0 && (p[d] < 0 || p[d] >= G.n[d])) {
-            p[d] = ((p[d] % G.n[d]) + G.n[d]) % G.n[d];
-            moved = true;
-        }
+    if (tid >= (long)c0 * c1) return;
+    const int i = lo0 + (int)(tid % c0);
+    const int j = lo1 + (int)(tid / c0);
+    const Coord<Y> X{xyz, C};
+    const long co = C.cbase + i + j * C.csd[1];
+    met_store<2>(G, met + 0 * G.vol, i, j, 0, X.D(1, 1, co));
+    met_store<2>(G, met + 1 * G.vol, i, j, 0, -X.D(0, 1, co));
+    met_store<2>(G, met + 2 * G.vol, i, j, 0, -X.D(1, 0, co));
+    met_store<2>(G, met + 3 * G.vol, i, j, 0, X.D(0, 0, co));
+    // 1/J = 1/2 [ (x y_eta - y x_eta)_xi + (y x_xi - x y_xi)_eta ]
+    double a = 0.0, b = 0.0;
+#pragma unroll
+    for (int m = 1; m <= Y / 2; ++m) {
+        const long p = co + m * C.csd[0], q = co - m * C.csd[0];
+        a += dcoef<Y>(m) * ((X.X(0, p) * X.D(1, 1, p) - X.X(1, p) * X.D(0, 1, p)) -
+                            (X.X(0, q) * X.D(1, 1, q) - X.X(1, q) * X.D(0, 1, q)));
+        const long r = co + m * C.csd[1], s = co - m * C.csd[1];
+        b += dcoef<Y>(m) * ((X.X(1, r) * X.D(0, 0, r) - X.X(0, r) * X.D(1, 0, r)) -
+                            (X.X(1, s) * X.D(0, 0, s) - X.X(0, s) * X.D(1, 0, s)));
     }
-    if (!moved) return;
-    const long src = G.base + p[0] + p[1] * G.sd[1] + (long)p[2] * G.sd[2];
-    for (int v = 0; v < nvar; ++v) a[v * G.vol + tid] = a[v * G.vol + src];
+    met_store<2>(G, met + 4 * G.vol, i, j, 0, 0.5 * (a + b));
+}
+
+// 3D metrics.  With (d, e, f) and (c, a, b) cyclic,
+//   P_{c,e} = a_e b - a b_e            (the pairing of eq. JBabc),
+//   s_{d,c} = 1/2 [ (P_{c,e})_f - (P_{c,f})_e ],
+//   1/J     = 1/3 sum_d (x . s_d)_d    (eq. JB).
+// The three derivatives of a term run along three different axes, so a node
+// reaches the coordinates of the box of half width Y/2 around it and no
+// further.  Evaluated node by node, each P and each s_d is recomputed by the
+// Y, Y^2 neighbours that use it; here a workgroup owns a tile of nodes and
+// forms every P_{c,e} and every x . s_d of its box once, in LDS, one
+// component c at a time (two coordinates, three P and the running x . s_d
+// are held).  Bound by the LDS reads of the differences.  The tile is 16
+// nodes along i, for whole cache lines, and 4 x 4 across, which keeps two
+// workgroups on a CU up to sixth order.
+template <int Y>
+struct MetTile {
+    static constexpr int H = Y / 2, TI = 16, TJ = 4, TK = 4, THREADS = 512;
+    static constexpr int BI = TI + Y, BJ = TJ + Y, BK = TK + Y;  // the box of the tile
+    double X[2][BK][BJ][BI];  // coordinates a, b of the box
+    // P_{c,e}: the tile's extent along e, the box's along the other axes
+    double P0[BK][BJ][TI], P1[BK][TJ][BI], P2[TK][BJ][BI];
+    // x . s_d: the box's extent along d, the tile's along the other axes
+    double S0[TK][TJ][BI], S1[TK][BJ][TI], S2[BK][TJ][TI];
+};
+
+// central difference along a stride (in doubles) at p
+template <int Y>
+__device__ __forceinline__ double met_diff(const double* p, int st) {
+    double s = 0.0;
+#pragma unroll
+    for (int m = 1; m <= Y / 2; ++m) s += dcoef<Y>(m) * (p[m * st] - p[-m * st]);
+    return s;
+}
+
+template <int Y>
+__global__ __launch_bounds__(MetTile<Y>::THREADS) void k_metrics3(GeoK G, CGeoK C, const double* __restrict__ xyz,
+                                                                  double* __restrict__ met, int lo0, int lo1,
+                                                                  int lo2, int c0, int c1, int c2) {
+    using M = MetTile<Y>;
+    constexpr int H = M::H, TI = M::TI, TJ = M::TJ, TK = M::TK, BI = M::BI, BJ = M::BJ, BK = M::BK;
+    constexpr int XJ = BI, XK = BI * BJ;  // strides of the box
+    __shared__ M L;
+    const unsigned nti = (unsigned)(c0 + TI - 1) / TI, ntj = (unsigned)(c1 + TJ - 1) / TJ;
+    const unsigned tile = (unsigned)xcd_block(blockIdx.x, gridDim.x);
+    // the tile's first node, counted from node (lo0, lo1, lo2)
+    const int ti = (int)(tile % nti) * TI, tj = (int)(tile / nti % ntj) * TJ, tk = (int)(tile / nti / ntj) * TK;
+    const int tid = (int)threadIdx.x;
+    // offset of box node (i, j, k) in a coordinate array, clamped to the
+    // nodes that the computed nodes reach (tiles may hang over the end)
+    auto coff = [&](int i, int j, int k) {
+        return C.cbase + (lo0 - H + min(ti + i, c0 - 1 + Y)) + (long)(lo1 - H + min(tj + j, c1 - 1 + Y)) * C.csd[1] +
+               (long)(lo2 - H + min(tk + k, c2 - 1 + Y)) * C.csd[2];
+    };
+#pragma unroll 1
+    for (int c = 0; c < 3; ++c) {
+        const double* xa = xyz + (c == 2 ? 0 : c + 1) * C.cvol;
+        const double* xb = xyz + (c == 0 ? 2 : c - 1) * C.cvol;
+        const double* xc = xyz + c * C.cvol;
+        for (int t = tid; t < BI * BJ * BK; t += M::THREADS) {
+            const long o = coff(t % BI, t / BI % BJ, t / (BI * BJ));
+            (&L.X[0][0][0][0])[t] = xa[o];
+            (&L.X[1][0][0][0])[t] = xb[o];
+        }
+        __syncthreads();
+        auto pair = [&](int i, int j, int k, int st) {
+            const double *a = &L.X[0][k][j][i], *b = &L.X[1][k][j][i];
+            return met_diff<Y>(a, st) * *b - *a * met_diff<Y>(b, st);
+        };
+        for (int t = tid; t < BK * BJ * TI; t += M::THREADS)
+            (&L.P0[0][0][0])[t] = pair(t % TI + H, t / TI % BJ, t / (TI * BJ), 1);
+        for (int t = tid; t < BK * TJ * BI; t += M::THREADS)
+            (&L.P1[0][0][0])[t] = pair(t % BI, t / BI % TJ + H, t / (BI * TJ), XJ);
+        for (int t = tid; t < TK * BJ * BI; t += M::THREADS)
+            (&L.P2[0][0][0])[t] = pair(t % BI, t / BI % BJ, t / (BI * BJ) + H, XK);
+        __syncthreads();
+        // s_{d,c} on the box's extent along d: its part of x . s_d, and the
+        // tile's own nodes to memory
+        auto put = [&](int d, int i, int j, int k, double s, double& acc) {
+            const double xs = xc[coff(i, j, k)] * s;
+            acc = c == 0 ? xs : acc + xs;
+            const int ni = i - H, nj = j - H, nk = k - H;
+            if (ni >= 0 && ni < TI && nj >= 0 && nj < TJ && nk >= 0 && nk < TK && ti + ni < c0 && tj + nj < c1 &&
+                tk + nk < c2)
+                met_store<3>(G, met + (3 * d + c) * G.vol, lo0 + ti + ni, lo1 + tj + nj, lo2 + tk + nk, s);
+        };
+        for (int t = tid; t < TK * TJ * BI; t += M::THREADS) {  // d = 0: (P_{c,1})_2 - (P_{c,2})_1
+            const int i = t % BI, j = t / BI % TJ + H, k = t / (BI * TJ) + H;
+            const double s = 0.5 * (met_diff<Y>(&L.P1[k][j - H][i], TJ * BI) - met_diff<Y>(&L.P2[k - H][j][i], BI));
+            put(0, i, j, k, s, (&L.S0[0][0][0])[t]);
+        }
+        for (int t = tid; t < TK * BJ * TI; t += M::THREADS) {  // d = 1: (P_{c,2})_0 - (P_{c,0})_2
+            const int i = t % TI + H, j = t / TI % BJ, k = t / (TI * BJ) + H;
+            const double s = 0.5 * (met_diff<Y>(&L.P2[k - H][j][i], 1) - met_diff<Y>(&L.P0[k][j][i - H], BJ * TI));
+            put(1, i, j, k, s, (&L.S1[0][0][0])[t]);
+        }
+        for (int t = tid; t < BK * TJ * TI; t += M::THREADS) {  // d = 2: (P_{c,0})_1 - (P_{c,1})_0
+            const int i = t % TI + H, j = t / TI % TJ + H, k = t / (TI * TJ);
+            const double s = 0.5 * (met_diff<Y>(&L.P0[k][j][i - H], TI) - met_diff<Y>(&L.P1[k][j - H][i], 1));
+            put(2, i, j, k, s, (&L.S2[0][0][0])[t]);
+        }
+        // the next component's loads overwrite X (read before the second
+        // barrier) and its pairs P: every difference above must be done
+        __syncthreads();
+    }
+    for (int t = tid; t < TK * TJ * TI; t += M::THREADS) {
+        const int i = t % TI, j = t / TI % TJ, k = t / (TI * TJ);
+        if (ti + i >= c0 || tj + j >= c1 || tk + k >= c2) continue;
+        const double J = met_diff<Y>(&L.S0[k][j][i + H], 1) + met_diff<Y>(&L.S1[k][j + H][i], TI) +
+                         met_diff<Y>(&L.S2[k + H][j][i], TJ * TI);
+        met_store<3>(G, met + 9 * G.vol, lo0 + ti + i, lo1 + tj + j, lo2 + tk + k, J / 3.0);
+    }
+}
+template <int Y>
+inline long met_tiles(const int c[3]) {
+    using M = MetTile<Y>;
+    return (long)((c[0] + M::TI - 1) / M::TI) * ((c[1] + M::TJ - 1) / M::TJ) * ((c[2] + M::TK - 1) / M::TK);
 }
 
 // Nodes of the ghost slabs of the frozen axes: for each frozen axis d, the
@@ -411,14 +497,6 @@ __global__ void k_time_advance(double* T, double dt) {
 // ---------------------------------------------------------------------------
 // viscous fluxes (periodic axes): node fluxes, then their central difference
 // ---------------------------------------------------------------------------
-
-// XCD-aware workgroup order: the dispatcher hands workgroups to the 8 XCDs
-// round-robin (b -> XCD b mod 8), each XCD with its own L2.  Renumbering
-// gives XCD x a contiguous range of the work instead of every eighth item.
-__device__ __forceinline__ long xcd_block(long b, long nb) {
-    const long per = nb / 8, rem = nb % 8, x = b % 8;
-    return x * per + (x < rem ? x : rem) + b / 8;
-}
 
 // The node of this thread in the viscous kernels: a workgroup of 256 takes
 // 64 (i) x 4 (j) nodes of one plane k.  The grid is cut into pencils of
