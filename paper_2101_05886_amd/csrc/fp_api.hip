@@ -177,6 +177,8 @@ SchemeK make_sk(const fp_scheme* s) {
     k.gamma = s->gamma;
     k.eps = s->weno_eps;
     k.reform = s->reformulated;
+    k.sg = std::sqrt(s->gamma);
+    k.igm1 = 1.0 / (s->gamma - 1.0);
     k.glf = nullptr;  // bound by bind_speeds once the arguments are checked
     return k;
 }
@@ -362,7 +364,6 @@ hipError_t run_rk3(const Ctx& c, const double* met, double* q, double* work, dou
     const double t0 = tdev ? 0.0 : t;
     const double stage_t[3] = {t0, t0 + dt, t0 + 0.5 * dt};
     if (ghosts) launch_run_start(c, q, work, s, probe);
-    const double* metV = met + (size_t)(c.grid.ndim == 3 ? 9 : 4) * c.G.vol;
     const double* in[3] = {q, A, B};
     double* out[3] = {A, B, q};
     const double ca[3] = {0.0, 3.0 / 4.0, 1.0 / 3.0};
@@ -373,7 +374,6 @@ hipError_t run_rk3(const Ctx& c, const double* met, double* q, double* work, dou
         EpiK e = epi(EPI_LAST_RK, R);
         e.stage0 = k == 0;
         e.out = out[k];
-        e.metV = metV;
         e.qin = in[k];
         e.qn = q;
         e.dt = dt;
@@ -836,7 +836,6 @@ fp_status fp_residual(const fp_grid* g, const fp_scheme* sch, const double* met,
     if (st) return st;
     EpiK last = epi(EPI_LAST_RES, dqdt);
     last.out = dqdt;
-    last.metV = met + (size_t)(g->ndim == 3 ? 9 : 4) * c.G.vol;
     hipError_t e = run_residual(c, met, q, dqdt, last, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "fp_residual launch");
     return FP_OK;
@@ -1156,7 +1155,6 @@ fp_status fp_viscous_residual(const fp_grid* g, const fp_scheme* sch, const doub
     if (st) return st;
     EpiK last = epi(EPI_LAST_RES, dqdt);
     last.out = dqdt;
-    last.metV = met + (size_t)(g->ndim == 3 ? 9 : 4) * c.G.vol;
     hipError_t e = run_residual(c, met, q, dqdt, last, (hipStream_t)stream, vwork);
     if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "fp_viscous_residual launch");

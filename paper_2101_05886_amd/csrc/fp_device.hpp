@@ -3,7 +3,9 @@
 //
 // One face i+1/2 of one grid line is evaluated by one lane.  The lane reads
 // the stencil nodes through a loader (slot r = 0..7 <-> node i-3+r) phase by
-// phase, so that only the values of the current phase are live in registers:
+// phase, so that only the values of the current phase are live in registers.
+// A node comes as primitives (Prim), which the sweeps form once per node
+// instead of once per face that uses it:
 //   A. cell-face 1/J, metrics and Q~ = Q/J by the central interpolation of
 //      the metric order Y; reference state Q* = Q~_f/(1/J)_f and reference
 //      face flux F~*_f = F(Q*) s_f                                    [FP64]
@@ -24,6 +26,8 @@ struct SchemeK {
     double gamma;
     double eps;
     int reform;  // 1: reference state subtracted (the paper); 0: standard scheme
+    double sg;   // sqrt(gamma)
+    double igm1; // 1 / (gamma - 1)
     // floor of the Lax-Friedrichs speeds of the sweep direction (u_n - c,
     // u_n, u_n + c): the face takes max(local speed, floor).  With global
     // speeds the floor is the block's largest local speed, so the face takes
@@ -93,6 +97,45 @@ __device__ __forceinline__ double vsqrt<double>(double x) { return sqrt(x); }
 template <>
 __device__ __forceinline__ float vsqrt<float>(float x) { return fast_sqrt(x); }
 
+// Primitives of a node: density, velocity, specific total energy E/rho and
+// the signed thermal speed ct = sign(r) sqrt|r|, r = p/rho, so that
+// r = ct |ct|, p = rho ct |ct| also where p < 0, and the sound speed is
+// sqrt(gamma) ct for r > 0, else 0.
+template <int DIM>
+struct Prim {
+    double rho, u[DIM], e, ct;
+};
+
+// sign(x) sqrt|x|: Newton steps on the hardware estimate of 1/sqrt|x| and
+// one residual correction (Goldschmidt's form), within a rounding or two
+__device__ __forceinline__ double signed_sqrt(double x) {
+    const double a = fabs(x);
+    double y = __builtin_amdgcn_rsq(a);
+    double g = a * y, h = 0.5 * y;
+    double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, a), h, g);
+    return a > 0.0 ? copysign(g, x) : 0.0 * x;
+}
+
+template <int DIM>
+__device__ __forceinline__ void to_prim(const double (&q)[DIM + 2], double gm1, Prim<DIM>& P) {
+    const double ir = drcp(q[0]);
+    double k2 = 0.0;
+    P.rho = q[0];
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) {
+        P.u[c] = q[1 + c] * ir;
+        k2 = fma(P.u[c], P.u[c], k2);
+    }
+    P.e = q[DIM + 1] * ir;
+    P.ct = signed_sqrt(gm1 * fma(-0.5, k2, P.e));
+}
+
 // central face interpolation weights of order Y on slot r (node i in slot 3)
 template <int Y>
 __device__ __forceinline__ constexpr double iw(int r) {
@@ -121,14 +164,14 @@ __device__ __forceinline__ constexpr double iw(int r) {
 // c_k = C_k (6 q_k), and the denominator carries 6 C_k.
 // FP64: weights C_k/(beta_k+eps)^2 normalised over one common denominator
 // (products of the squared indicators), one reciprocal per reconstruction.
+// The window enters through its first differences, the candidates relative to
+// c, which comes back at the end: five operations fewer than from the values.
 __device__ __forceinline__ double weno5(double a, double b, double c, double d, double e,
                                         double eps16) {
-    const double c0 = 0.2 * a - 0.7 * b + 1.1 * c;
-    const double c1 = -0.6 * b + 3.0 * c + 1.2 * d;
-    const double c2 = 0.6 * c + 1.5 * d - 0.3 * e;
-    const double t0 = a - 2.0 * b + c, s0 = a - 4.0 * b + 3.0 * c;
-    const double t1 = b - 2.0 * c + d, s1 = d - b;
-    const double t2 = c - 2.0 * d + e, s2 = 3.0 * c - 4.0 * d + e;
+    const double f1 = b - a, f2 = c - b, f3 = d - c, f4 = e - d;
+    const double t0 = f2 - f1, t1 = f3 - f2, t2 = f4 - f3;
+    const double s0 = fma(3.0, f2, -f1), s1 = f2 + f3, s2 = fma(3.0, f3, -f4);
+    const double c0 = fma(0.5, f2, -0.2 * f1), c1 = fma(1.2, f3, 0.6 * f2), c2 = fma(1.2, f3, -0.3 * f4);
     const double k = 13.0 / 3.0;
     double d0 = fma(k * t0, t0, fma(s0, s0, eps16));
     double d1 = fma(k * t1, t1, fma(s1, s1, eps16));
@@ -139,10 +182,14 @@ __device__ __forceinline__ double weno5(double a, double b, double c, double d, 
     const double p0 = d1 * d2, p1 = d0 * d2, p2 = d0 * d1;
     const double num = fma(p0, c0, fma(p1, c1, p2 * c2));
     const double den = fma(p0, 0.6, fma(p1, 3.6, p2 * 1.8));
-    return num * drcp1(den);
+    return fma(num, drcp1(den), c);
 }
 
-// FP32 form: reciprocal weights (no overflow of the products for large beta)
+// FP32 form: reciprocal weights (no overflow of the products for large beta),
+// candidates from the values themselves.  The reference subtraction leaves
+// values near zero beside the face, so differences of neighbours are larger
+// than c and d and round coarser: the difference form of the FP64 path raises
+// the FP32 error of the flux 1.3 to 1.5 times.
 __device__ __forceinline__ float weno5(float a, float b, float c, float d, float e, float eps16) {
     const float c0 = 0.2f * a - 0.7f * b + 1.1f * c;
     const float c1 = -0.6f * b + 3.0f * c + 1.2f * d;
@@ -271,16 +318,7 @@ __device__ __forceinline__ void face_ref(const LD& ld, const SchemeK& sk, FaceRe
 #pragma unroll
     for (int v = 0; v < NV; ++v) Qt[v] = 0.0;
 #pragma unroll
-    for (int r = r0; r < r1; ++r) {
-        double q[NV], V, s[DIM];
-        ld.slot(r, q, V, s);
-        const double w = iw<Y>(r);
-        Vf += w * V;
-#pragma unroll
-        for (int c = 0; c < DIM; ++c) sf[c] += w * s[c];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) Qt[v] += w * (q[v] * V);
-    }
+    for (int r = r0; r < r1; ++r) ld.interp(r, iw<Y>(r), Qt, Vf, sf);
     R.Vf = Vf;
 #pragma unroll
     for (int c = 0; c < DIM; ++c) R.sf[c] = sf[c];
@@ -331,45 +369,21 @@ struct Eig {
 template <int DIM, typename T, class LD>
 __device__ __forceinline__ void roe(const LD& ld, const SchemeK& sk, const FaceRef<DIM>& R,
                                     Eig<DIM, T>& S) {
-    constexpr int NV = DIM + 2, E = NV - 1;
     const double gm1 = sk.gamma - 1.0;
     const double isn = drsq1(R.s2);  // 1/|s_f|
 #pragma unroll
     for (int c = 0; c < DIM; ++c) S.n[c] = T(R.sf[c] * isn);
     S.sigma = T(R.s2 * isn * drcp1(R.Vf));
-    double uL[DIM], uR[DIM], HL, HR, rL, rR;
-    {
-        double q[NV], V, s[DIM];
-        ld.slot(3, q, V, s);
-        const double ir = drcp(q[0]);
-        double m2 = 0.0;
-#pragma unroll
-        for (int c = 0; c < DIM; ++c) {
-            uL[c] = q[1 + c] * ir;
-            m2 += q[1 + c] * uL[c];
-        }
-        HL = (q[E] + gm1 * (q[E] - 0.5 * m2)) * ir;
-        rL = q[0];
-    }
-    {
-        double q[NV], V, s[DIM];
-        ld.slot(4, q, V, s);
-        const double ir = drcp(q[0]);
-        double m2 = 0.0;
-#pragma unroll
-        for (int c = 0; c < DIM; ++c) {
-            uR[c] = q[1 + c] * ir;
-            m2 += q[1 + c] * uR[c];
-        }
-        HR = (q[E] + gm1 * (q[E] - 0.5 * m2)) * ir;
-        rR = q[0];
-    }
-    const T wL = T(rL) * rsq1<T>(T(rL)), wR = T(rR) * rsq1<T>(T(rR));
+    Prim<DIM> L, Q;
+    ld.prim(3, L);
+    ld.prim(4, Q);
+    const double HL = fma(L.ct, fabs(L.ct), L.e), HR = fma(Q.ct, fabs(Q.ct), Q.e);
+    const T wL = T(L.rho) * rsq1<T>(T(L.rho)), wR = T(Q.rho) * rsq1<T>(T(Q.rho));
     const T iwr = rcp1<T>(wL + wR);
     T q2 = T(0), un = T(0);
 #pragma unroll
     for (int c = 0; c < DIM; ++c) {
-        S.uh[c] = (wL * T(uL[c]) + wR * T(uR[c])) * iwr;
+        S.uh[c] = (wL * T(L.u[c]) + wR * T(Q.u[c])) * iwr;
         q2 += S.uh[c] * S.uh[c];
         un += S.uh[c] * S.n[c];
     }
@@ -415,6 +429,16 @@ __device__ __forceinline__ void roe(const LD& ld, const SchemeK& sk, const FaceR
 // phase C helper: reference-subtracted values and LF speeds at one node
 // ---------------------------------------------------------------------------
 
+// n.u and the sound speed of a node
+template <int DIM, typename T>
+__device__ __forceinline__ void node_speeds(const SchemeK& sk, const Eig<DIM, T>& S, const Prim<DIM>& P, T& un,
+                                            T& cs) {
+    un = T(0);
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) un += S.n[c] * T(P.u[c]);
+    cs = T(sk.sg) * fmax(T(P.ct), T(0));
+}
+
 template <int DIM, typename T>
 struct NodeDiff {
     double dQ[DIM + 2], dF[DIM + 2];
@@ -426,32 +450,28 @@ __device__ __forceinline__ void node_diff(const LD& ld, int r, const SchemeK& sk
                                           const FaceRef<DIM>& R, const Eig<DIM, T>& S,
                                           NodeDiff<DIM, T>& N) {
     constexpr int NV = DIM + 2, E = NV - 1;
-    const double gm1 = sk.gamma - 1.0;
-    double q[NV], V, s[DIM];
-    ld.slot(r, q, V, s);
-    const double ir = drcp(q[0]);
-    double u[DIM], m2 = 0.0, U = 0.0, Us = 0.0;
+    Prim<DIM> P;
+    double V, s[DIM];
+    ld.prim(r, P);
+    ld.metric(r, V, s);
+    double U = 0.0, Us = 0.0;
 #pragma unroll
     for (int c = 0; c < DIM; ++c) {
-        u[c] = q[1 + c] * ir;
-        m2 += q[1 + c] * u[c];
-        U += u[c] * s[c];
+        U += P.u[c] * s[c];
         Us += R.us[c] * s[c];
     }
-    const double p = gm1 * (q[E] - 0.5 * m2);
+    const double p = P.rho * P.ct * fabs(P.ct);
     const double dp = p - R.ps;
-    N.dF[0] = q[0] * U - R.Qs[0] * Us;
+    const double m = P.rho * U;
+    N.dF[0] = m - R.Qs[0] * Us;
 #pragma unroll
-    for (int c = 0; c < DIM; ++c) N.dF[1 + c] = q[1 + c] * U - R.Qs[1 + c] * Us + dp * s[c];
-    N.dF[E] = (q[E] + p) * U - (R.Qs[E] + R.ps) * Us;
+    for (int c = 0; c < DIM; ++c) N.dF[1 + c] = m * P.u[c] - R.Qs[1 + c] * Us + dp * s[c];
+    N.dF[E] = m * P.e + p * U - (R.Qs[E] + R.ps) * Us;
+    N.dQ[0] = (P.rho - R.Qs[0]) * V;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) N.dQ[v] = (q[v] - R.Qs[v]) * V;
-    T un = T(0);
-#pragma unroll
-    for (int c = 0; c < DIM; ++c) un += S.n[c] * T(u[c]);
-    N.un = un;
-    const T c2 = T(sk.gamma * p * ir);
-    N.cs = c2 > T(0) ? c2 * rsq1<T>(c2) : T(0);
+    for (int c = 0; c < DIM; ++c) N.dQ[1 + c] = fma(P.rho, P.u[c], -R.Qs[1 + c]) * V;
+    N.dQ[E] = fma(P.rho, P.e, -R.Qs[E]) * V;
+    node_speeds<DIM, T>(sk, S, P, N.un, N.cs);
 }
 
 // l_s . w for the five (four in 2D) fields, using the structure of the Euler
@@ -639,6 +659,13 @@ __device__ __forceinline__ void face_flux_weno7(const LD& ld, const SchemeK& sk,
 //   sum_s r_s (h+_s + h-_s) = central6(dF~) + (1/60) R Lambda L Delta^5(dQ~),
 // which is the linear-upwind member of eq. new_form_linear_upwind.
 
+// The central sum is linear in the node fluxes, so the reference flux leaves
+// it as one term per face: central6(dF~) = central6(F~) - F(Q*).s6 with
+// s6 = central6(s).  With the add-back F(Q*).s_f the flux keeps
+// F(Q*).(s_f - s6), which vanishes for sixth-order metrics, whose
+// interpolation is central6 itself.  (The fifth difference takes Q - Q* node
+// by node: its weights would amplify the rounding of Q.)
+
 template <int DIM, int Y, typename T, class LD>
 __device__ __forceinline__ void face_flux_lu5(const LD& ld, const SchemeK& sk,
                                               double (&Fo)[DIM + 2]) {
@@ -649,24 +676,54 @@ __device__ __forceinline__ void face_flux_lu5(const LD& ld, const SchemeK& sk,
     face_ref<DIM, Y>(ld, sk, R);
     Eig<DIM, T> S;
     roe<DIM, T>(ld.after(R.Vf), sk, R, S);
-    double cen[NV], del[NV];
+    double cen[NV], del[NV], s6[DIM];
 #pragma unroll
     for (int v = 0; v < NV; ++v) cen[v] = del[v] = 0.0;
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) s6[c] = 0.0;
     T mxm = T(0), mx0 = T(0), mxp = T(0);
     double chain = double(S.pI);
 #pragma unroll
     for (int r = 1; r <= 6; ++r) {
-        NodeDiff<DIM, T> N;
-        node_diff<DIM, T>(ld.after(chain), r, sk, R, S, N);
-        chain = N.dQ[0];
-        mxm = fmax(mxm, fabs(N.un - N.cs));
-        mx0 = fmax(mx0, fabs(N.un));
-        mxp = fmax(mxp, fabs(N.un + N.cs));
+        const LD ln = ld.after(chain);
+        Prim<DIM> P;
+        double V, s[DIM], U = 0.0;
+        ln.prim(r, P);
+        ln.metric(r, V, s);
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            cen[v] += c6[r - 1] * N.dF[v];
-            del[v] += d5[r - 1] * N.dQ[v];
+        for (int c = 0; c < DIM; ++c) U += P.u[c] * s[c];
+        const double wr = c6[r - 1] * P.rho, wm = wr * U, rr = P.ct * fabs(P.ct), wp = wr * rr;
+        cen[0] += wm;
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) cen[1 + c] = fma(wm, P.u[c], fma(wp, s[c], cen[1 + c]));
+        cen[E] = fma(wm, P.e + rr, cen[E]);
+        const double wV = d5[r - 1] * V;
+        del[0] = fma(wV, P.rho - R.Qs[0], del[0]);
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) del[1 + c] = fma(wV, fma(P.rho, P.u[c], -R.Qs[1 + c]), del[1 + c]);
+        del[E] = fma(wV, fma(P.rho, P.e, -R.Qs[E]), del[E]);
+        if constexpr (Y != 6) {
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) s6[c] += c6[r - 1] * s[c];
         }
+        chain = del[0];
+        T un, cs;
+        node_speeds<DIM, T>(sk, S, P, un, cs);
+        mxm = fmax(mxm, fabs(un - cs));
+        mx0 = fmax(mx0, fabs(un));
+        mxp = fmax(mxp, fabs(un + cs));
+    }
+    if constexpr (Y != 6) {
+        double U = 0.0;
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) {
+            s6[c] = R.sf[c] - s6[c];
+            U += R.us[c] * s6[c];
+        }
+        cen[0] = fma(R.Qs[0], U, cen[0]);
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) cen[1 + c] = fma(R.Qs[1 + c], U, fma(R.ps, s6[c], cen[1 + c]));
+        cen[E] = fma(R.Qs[E] + R.ps, U, cen[E]);
     }
     T w[NV], pa[NV];
 #pragma unroll
@@ -682,7 +739,7 @@ __device__ __forceinline__ void face_flux_lu5(const LD& ld, const SchemeK& sk,
     T o[NV];
     backproject<DIM, T>(S, pa, o);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) Fo[v] = R.Fts[v] + cen[v] + double(o[v]) * (1.0 / 60.0);
+    for (int v = 0; v < NV; ++v) Fo[v] = fma(double(o[v]), 1.0 / 60.0, cen[v]);
 }
 
 template <int DIM, int RECON, int Y, typename T, class LD>

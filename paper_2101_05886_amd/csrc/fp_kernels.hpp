@@ -45,15 +45,13 @@ struct GeoK {
 //             out = u (first stage) or a qn + b u (TVD RK3 stages 2, 3)
 enum { EPI_FIRST = 0, EPI_MID = 1, EPI_LAST_RES = 2, EPI_LAST_RK = 3 };
 
-// The eta / zeta sweeps, which apply the final epilogues, take qin and 1/J
-// from the stencil rows they staged: qin must be the array the sweep reads
-// and metV the metric array's 1/J component.
+// The eta / zeta sweeps, which apply the final epilogues, take 1/J from the
+// stencil rows they staged.
 struct EpiK {
     int mode;
     int stage0;
     double* R;
     double* out;
-    const double* metV;
     const double* qin;
     const double* qn;
     double dt, a, b;
@@ -107,26 +105,26 @@ struct EpiPre {
     double R[NV], qin[NV], qn[NV], V;
 };
 
-// (own_qv: the caller supplies 1/J and the stage input itself, from values
-// it has staged already)
+// (the final epilogues' callers supply 1/J from the rows they staged; they
+// may take the stage input later, with epi_load_qin)
 // (buffer loads and stores: one 32-bit byte offset per lane serves every
 // variable array, whose base goes into the wave-uniform resource)
 template <int NV>
-__device__ __forceinline__ void epi_load(const EpiK& ep, long vol, long off, EpiPre<NV>& p,
-                                         bool own_qv = false) {
+__device__ __forceinline__ void epi_load_qin(const EpiK& ep, long vol, long off, EpiPre<NV>& p) {
+    if (ep.mode != EPI_LAST_RK) return;
+    const double* qin = rebase(ep.qin);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) p.qin[v] = ldb(qin + v * vol, vol, (unsigned)off * 8u);
+}
+template <int NV>
+__device__ __forceinline__ void epi_load(const EpiK& ep, long vol, long off, EpiPre<NV>& p, bool with_qin) {
     if (ep.mode == EPI_FIRST) return;
     const unsigned bo = (unsigned)off * 8u;
     const double* R = rebase(ep.R);
 #pragma unroll
     for (int v = 0; v < NV; ++v) p.R[v] = ldb(R + v * vol, vol, bo);
-    if (ep.mode == EPI_MID) return;
-    if (!own_qv) p.V = ldb(rebase(ep.metV), vol, bo);
-    if (ep.mode == EPI_LAST_RES) return;
-    if (!own_qv) {
-        const double* qin = rebase(ep.qin);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) p.qin[v] = ldb(qin + v * vol, vol, bo);
-    }
+    if (ep.mode != EPI_LAST_RK) return;
+    if (with_qin) epi_load_qin<NV>(ep, vol, off, p);
     if (ep.stage0) return;
     const double* qn = rebase(ep.qn);
 #pragma unroll
@@ -185,11 +183,12 @@ struct LineLoader {
     int i;          // the face is i+1/2
     int nd;         // interior nodes along the line
     int per;        // periodic axis
+    double gm1;     // gamma - 1
 
     __device__ __forceinline__ LineLoader(const GeoK& G, const double* met_, const double* q_,
-                                          long lb_, int i_)
+                                          long lb_, int i_, double gamma)
         : met(met_), q(q_), vol(G.vol), lb((unsigned)lb_), sd((int)G.sd[DIR]), i(i_),
-          nd(G.n[DIR]), per(G.bc[DIR] == 0) {}
+          nd(G.n[DIR]), per(G.bc[DIR] == 0), gm1(gamma - 1.0) {}
 
     // A copy whose loads cannot be hoisted above, or merged with loads
     // before, the computation of `dep`: the line offset passes through an
@@ -201,19 +200,69 @@ struct LineLoader {
         return c;
     }
 
-    __device__ __forceinline__ void slot(int r, double (&qv)[DIM + 2], double& V,
-                                         double (&s)[DIM]) const {
-        constexpr int NMET = DIM == 3 ? 10 : 5;
+    __device__ __forceinline__ void cons(int r, double (&qv)[DIM + 2]) const {
         const int t = i - 3 + r;
         int tt = t;
         if (per) tt = t < 0 ? t + nd : (t >= nd ? t - nd : t);
         const unsigned off = (lb + (unsigned)(tt * sd)) * 8u;
-        const unsigned moff = (lb + (unsigned)(t * sd)) * 8u;
 #pragma unroll
         for (int v = 0; v < DIM + 2; ++v) qv[v] = ldb(q + v * vol, vol, off);
+    }
+    __device__ __forceinline__ void prim(int r, Prim<DIM>& P) const {
+        double qv[DIM + 2];
+        cons(r, qv);
+        to_prim<DIM>(qv, gm1, P);
+    }
+    __device__ __forceinline__ void metric(int r, double& V, double (&s)[DIM]) const {
+        constexpr int NMET = DIM == 3 ? 10 : 5;
+        const unsigned moff = (lb + (unsigned)((i - 3 + r) * sd)) * 8u;
         V = ldb(met + (NMET - 1) * vol, vol, moff);
 #pragma unroll
         for (int c = 0; c < DIM; ++c) s[c] = ldb(met + (DIR * DIM + c) * vol, vol, moff);
+    }
+    // adds slot r with weight w to the face values of Q/J, 1/J and s
+    __device__ __forceinline__ void interp(int r, double w, double (&Qt)[DIM + 2], double& Vf,
+                                           double (&sf)[DIM]) const {
+        double qv[DIM + 2], V, s[DIM];
+        cons(r, qv);
+        metric(r, V, s);
+        const double wV = w * V;
+        Vf += wV;
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) sf[c] += w * s[c];
+#pragma unroll
+        for (int v = 0; v < DIM + 2; ++v) Qt[v] = fma(wV, qv[v], Qt[v]);
+    }
+};
+
+// Slot access of a loader to nodes staged in LDS as primitives: `at(r, v)` is
+// value v of slot r in the order rho, u, e, 1/J, s, ct.
+template <int DIM, class LD>
+struct StagedNodes {
+    __device__ __forceinline__ const LD& self() const { return static_cast<const LD&>(*this); }
+    __device__ __forceinline__ void prim(int r, Prim<DIM>& P) const {
+        P.rho = self().at(r, 0);
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) P.u[c] = self().at(r, 1 + c);
+        P.e = self().at(r, DIM + 1);
+        P.ct = self().at(r, 2 * DIM + 3);
+    }
+    __device__ __forceinline__ void metric(int r, double& V, double (&s)[DIM]) const {
+        V = self().at(r, DIM + 2);
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) s[c] = self().at(r, DIM + 3 + c);
+    }
+    __device__ __forceinline__ void interp(int r, double w, double (&Qt)[DIM + 2], double& Vf,
+                                           double (&sf)[DIM]) const {
+        double V, s[DIM];
+        metric(r, V, s);
+        const double wV = w * V, wVr = wV * self().at(r, 0);
+        Vf += wV;
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) sf[c] += w * s[c];
+        Qt[0] += wVr;
+#pragma unroll
+        for (int c = 0; c <= DIM; ++c) Qt[1 + c] = fma(wVr, self().at(r, 1 + c), Qt[1 + c]);
     }
 };
 
@@ -228,6 +277,15 @@ using char_t = typename std::conditional<PREC == 1, float, double>::type;
 __device__ __forceinline__ void dma_dword(const double* var, long elems, void* lds, unsigned byteoff) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(buf(var, elems), (__attribute__((address_space(3))) void*)lds, 4,
                                              byteoff, 0, 0, 0);
+}
+
+// Barrier of a workgroup for its LDS traffic alone: unlike __syncthreads it
+// leaves global loads and stores in flight.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
 
 // The wave's index in its workgroup, as a value the compiler knows to be
@@ -253,8 +311,9 @@ __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane
 template <int DIM, int NE_>
 struct XLds {
     static constexpr int NE = NE_;          // staged entries per buffer
-    static constexpr int NS = 2 * DIM + 3;  // q, 1/J, s_xi
+    static constexpr int NS = 2 * DIM + 3;  // q, 1/J, s_xi; the state as primitives once converted
     double b[2][NS][NE];                    // double buffer: current item, next item
+    double ct[NE];                          // the thermal speed of the current item's nodes
 };
 __device__ __host__ constexpr int x_entries(int prec, int recon, int Y) {
     return FP_XWAVES(prec, recon, Y) == 3 ? 88 : 128;
@@ -292,35 +351,60 @@ __device__ __forceinline__ void line_step(unsigned a1, unsigned a2, unsigned dL,
     }
 }
 
-// The uniform geometry of xi item j.
+// The uniform geometry of a xi item: its first face F0 = L0 nf + f0 on line
+// L0 = a1 + n1 a2 (node 0 of that line at element `line`), its staged entries
+// e(F0) .. e(Fl) + 7, its faces, and whether the lines it touches pass the
+// last one of their plane.
 struct XItem {
-    unsigned F0, L0, f0, a1, a2, count;
+    unsigned f0, a1, a2, line, count, faces, wraps;
 };
 
+template <int NE>
 __device__ __forceinline__ XItem x_item(const GeoK& G, long j, int W) {
     XItem it;
-    const unsigned nf = (unsigned)G.n[0] + 1, ne = (unsigned)G.n[0] + 8, n1 = (unsigned)G.n[1];
+    const unsigned nf = (unsigned)G.n[0] + 1, n1 = (unsigned)G.n[1];
     const unsigned total = nf * n1 * (unsigned)G.n[2];
-    it.F0 = (unsigned)((W - 1) * j);
-    it.L0 = it.F0 / nf;
-    it.f0 = it.F0 - it.L0 * nf;
-    it.a1 = it.L0 % n1;
-    it.a2 = it.L0 / n1;
-    const unsigned Fl = min(it.F0 + (unsigned)W - 1, total - 1);
-    const unsigned Ll = Fl / nf;
-    it.count = (Ll - it.L0) * ne + (Fl - Ll * nf) + 8 - it.f0;  // entries e(F0) .. e(Fl) + 7
+    const unsigned F0 = (unsigned)((W - 1) * j);
+    const unsigned L0 = F0 / nf;
+    it.f0 = F0 - L0 * nf;
+    it.a2 = L0 / n1;
+    it.a1 = L0 - it.a2 * n1;
+    it.line = (unsigned)G.base + it.a1 * (unsigned)G.sd[1] + it.a2 * (unsigned)G.sd[2];
+    it.faces = min((unsigned)W, total - F0);
+    // the last face's line, counted from L0 (f0 + W < 2^20: see small_div)
+    unsigned dl = 0, fl = it.f0 + it.faces - 1;
+    while (fl >= nf) {
+        fl -= nf;
+        ++dl;
+    }
+    it.count = dl * 7 + it.faces + 7;
+    // (a staging pass runs past the last entry, so past the last line by
+    // (NE + 31) / (n0 + 8) lines at most)
+    it.wraps = it.a1 + dl + 1 + (NE + 31) / (nf + 7) >= n1;
     return it;
 }
 
-// Stage item j's stencil entries into buf (all 64 lanes; asynchronous).
+// Node 0 of line L0 + dL of an item, as an element offset; lines past the
+// block's last one (their entries are never read) take that one.
+__device__ __forceinline__ unsigned x_line(const GeoK& G, const XItem& it, unsigned dL) {
+    if (!it.wraps) return it.line + dL * (unsigned)G.sd[1];
+    unsigned l1, l2;
+    line_step(it.a1, it.a2, dL, (unsigned)G.n[1], l1, l2);
+    if (l2 >= (unsigned)G.n[2]) {
+        l1 = (unsigned)G.n[1] - 1;
+        l2 = (unsigned)G.n[2] - 1;
+    }
+    return (unsigned)G.base + l1 * (unsigned)G.sd[1] + l2 * (unsigned)G.sd[2];
+}
+
+// Stage an item's stencil entries into buf (all 64 lanes; asynchronous).
 template <int DIM, int NE>
 __device__ __forceinline__ void x_stage(const GeoK& G, const double* __restrict__ met, const double* qs,
-                                        long j, int W, double (*buf)[NE]) {
+                                        const XItem& it, double (*buf)[NE]) {
     constexpr int NV = DIM + 2;
     constexpr int NMET = DIM == 3 ? 10 : 5;
     const unsigned lane = threadIdx.x & 63;
-    const unsigned n0 = (unsigned)G.n[0], ne = n0 + 8, n1 = (unsigned)G.n[1], n2 = (unsigned)G.n[2];
-    const XItem it = x_item(G, j, W);
+    const unsigned n0 = (unsigned)G.n[0], ne = n0 + 8;
     const float inv_ne = 1.0f / (float)ne;
     const int g = G.g;
     const int per = G.bc[0] == 0;
@@ -334,19 +418,13 @@ __device__ __forceinline__ void x_stage(const GeoK& G, const double* __restrict_
         const unsigned k = it.f0 + 32u * p + (lane >> 1);  // from the start of line L0's entries
         const unsigned dL = small_div(k, inv_ne);
         const int x = (int)(k - dL * ne) - 4;
-        unsigned l1, l2;
-        line_step(it.a1, it.a2, dL, n1, l1, l2);
-        if (l2 >= n2) {  // entries past the last line are never read
-            l1 = n1 - 1;
-            l2 = n2 - 1;
-        }
         const int xm = x < -g ? -g : (x > (int)n0 - 1 + g ? (int)n0 - 1 + g : x);
         int xq = xm;
         if (per) {
             xq = x < 0 ? x + (int)n0 : (x >= (int)n0 ? x - (int)n0 : x);
             xq = xq < 0 ? 0 : (xq > (int)n0 - 1 ? (int)n0 - 1 : xq);
         }
-        const unsigned lb = (unsigned)G.base + l1 * (unsigned)G.sd[1] + l2 * (unsigned)G.sd[2];
+        const unsigned lb = x_line(G, it, dL);
         const unsigned oq = (lb + (unsigned)xq) * 8u + (lane & 1) * 4u;
         const unsigned om = (lb + (unsigned)xm) * 8u + (lane & 1) * 4u;
         const double* qp = rebase(qs);
@@ -359,10 +437,33 @@ __device__ __forceinline__ void x_stage(const GeoK& G, const double* __restrict_
     }
 }
 
+// Primitives of an item's entries in place of their conserved state: each
+// entry serves the six to eight faces around it.
+template <int DIM, int NE>
+__device__ __forceinline__ void x_convert(unsigned count, double gm1, double (*buf)[NE], double* ct) {
+    constexpr int NV = DIM + 2;
+    for (unsigned e = threadIdx.x & 63; e < count; e += 64) {
+        double q[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) q[v] = buf[v][e];
+        Prim<DIM> P;
+        to_prim<DIM>(q, gm1, P);
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) buf[1 + c][e] = P.u[c];
+        buf[NV - 1][e] = P.e;
+        ct[e] = P.ct;
+    }
+    // other lanes of the wave read these entries (LDS operations of a wave
+    // complete in order)
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // Stencil reads of one lane's xi face from the wave's staged entries.
 template <int DIM, int NE>
-struct XLoader {
+struct XLoader : StagedNodes<DIM, XLoader<DIM, NE>> {
     const double (*buf)[NE];
+    const double* ct;
     unsigned ea;  // byte offset of entry e(F) in a variable row
 
     __device__ __forceinline__ XLoader after(double dep) const {
@@ -371,14 +472,10 @@ struct XLoader {
         return c;
     }
 
-    __device__ __forceinline__ void slot(int r, double (&qv)[DIM + 2], double& V,
-                                         double (&s)[DIM]) const {
-        const char* row = reinterpret_cast<const char*>(&buf[0][0]) + ea + r * 8;
-#pragma unroll
-        for (int v = 0; v < DIM + 2; ++v) qv[v] = *reinterpret_cast<const double*>(row + v * NE * 8);
-        V = *reinterpret_cast<const double*>(row + (DIM + 2) * NE * 8);
-#pragma unroll
-        for (int c = 0; c < DIM; ++c) s[c] = *reinterpret_cast<const double*>(row + (DIM + 3 + c) * NE * 8);
+    __device__ __forceinline__ double at(int r, int v) const {
+        const char* row = v == 2 * DIM + 3 ? reinterpret_cast<const char*>(ct)
+                                           : reinterpret_cast<const char*>(&buf[0][0]) + v * NE * 8;
+        return *reinterpret_cast<const double*>(row + ea + r * 8);
     }
 };
 
@@ -387,16 +484,17 @@ struct XLoader {
 // comes first in a stage, so its epilogue is FIRST (ACC = false: R = -d,
 // nothing to load) or MID (ACC = true: R -= d, after the viscous part or a
 // caller's accumulation; R loads while the face is computed).
+//
+// The wave waits for its memory operations between the face and the stores:
+// the next item's entries, asked for before the face, have landed by then,
+// and no wait ever holds for a store that was just issued.
 template <int DIM, int RECON, int Y, int PREC, bool ACC>
-__device__ __forceinline__ void x_compute(const GeoK& G, const SchemeK& sk, const EpiK& ep, long j, int W,
-                                          const double (*buf)[x_entries(PREC, RECON, Y)]) {
+__device__ __forceinline__ void x_compute(const GeoK& G, const SchemeK& sk, const EpiK& ep, const XItem& it,
+                                          double (*buf)[x_entries(PREC, RECON, Y)], double* ct) {
     constexpr int NV = DIM + 2;
     const unsigned lane = threadIdx.x & 63;
     const unsigned nf = (unsigned)G.n[0] + 1, ne = (unsigned)G.n[0] + 8;
-    const unsigned total = nf * (unsigned)G.n[1] * (unsigned)G.n[2];
-    const XItem it = x_item(G, j, W);
-    const unsigned F = it.F0 + lane;
-    const bool active = lane < (unsigned)W && F < total;
+    const bool active = lane < it.faces;
     double fl[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) fl[v] = 0.0;
@@ -405,30 +503,32 @@ __device__ __forceinline__ void x_compute(const GeoK& G, const SchemeK& sk, cons
     const unsigned f = k - dL * nf;
     // lane l > 0 writes node f - 1, between its face and lane l - 1's
     const bool writes = active && lane > 0 && f > 0;
-    long noff = 0;
+    unsigned noff = 0;
     EpiPre<NV> pre;
+    x_convert<DIM, x_entries(PREC, RECON, Y)>(it.count, sk.gamma - 1.0, buf, ct);
     if (writes) {
-        unsigned l1, l2;
-        line_step(it.a1, it.a2, dL, (unsigned)G.n[1], l1, l2);
-        noff = G.base + (long)l1 * G.sd[1] + (long)l2 * G.sd[2] + (f - 1);
-        if (ACC) epi_load<NV>(epi_mid(ep), G.vol, noff, pre);
+        noff = x_line(G, it, dL) + (f - 1);
+        if (ACC) epi_load<NV>(epi_mid(ep), G.vol, noff, pre, false);
     }
     if (active) {
         XLoader<DIM, x_entries(PREC, RECON, Y)> ld;
         ld.buf = buf;
+        ld.ct = ct;
         ld.ea = (dL * ne + f - it.f0) * 8u;
         face_flux<DIM, RECON, Y, char_t<PREC>>(ld, sk, fl);
     }
     double d[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) d[v] = fl[v] - __shfl_up(fl[v], 1, 64);
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
     if (writes) {
         if (ACC) {
             epi_store<NV>(epi_mid(ep), G.vol, noff, pre, d);
         } else {
             double* R = rebase(ep.R);
 #pragma unroll
-            for (int v = 0; v < NV; ++v) stb(R + v * G.vol, G.vol, (unsigned)noff * 8u, -d[v]);
+            for (int v = 0; v < NV; ++v) stb(R + v * G.vol, G.vol, noff * 8u, -d[v]);
         }
     }
 }
@@ -450,12 +550,19 @@ void k_sweep_x(GeoK G, SchemeK sk, const double* __restrict__ met, const double*
     const int W = x_window(G.n[0], NE);
     long j = (long)blockIdx.x * 4 + wave_id();
     int cur = 0;
-    if (j < items) x_stage<DIM, NE>(G, met, qs, j, W, L.b[0]);
+    if (j >= items) return;
+    XItem it = x_item<NE>(G, j, W);
+    x_stage<DIM, NE>(G, met, qs, it, L.b[0]);
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
     for (; j < items; j += nw, cur ^= 1) {
-        __builtin_amdgcn_s_waitcnt(0);  // item j's entries are in LDS
-        asm volatile("" ::: "memory");
-        if (j + nw < items) x_stage<DIM, NE>(G, met, qs, j + nw, W, L.b[cur ^ 1]);
-        x_compute<DIM, RECON, Y, PREC, ACC>(G, sk, ep, j, W, L.b[cur]);
+        XItem next = it;
+        if (j + nw < items) {
+            next = x_item<NE>(G, j + nw, W);
+            x_stage<DIM, NE>(G, met, qs, next, L.b[cur ^ 1]);
+        }
+        x_compute<DIM, RECON, Y, PREC, ACC>(G, sk, ep, it, L.b[cur], L.ct);
+        it = next;
     }
 }
 
@@ -470,7 +577,11 @@ constexpr int wide_stencil(int recon, int Y) { return (recon == 2 || Y == 8) ? 1
 template <int DIM, int WIDE>
 struct WgLds {
     static constexpr int NV = DIM + 2;
-    static constexpr int NS = 2 * DIM + 3;   // values per node: q, 1/J, s_DIR
+    // values per node: the state as primitives, 1/J, s_DIR and, where the LDS
+    // has room beside two resident workgroups, the thermal speed; else that
+    // takes the place of E/rho, which the reads then rebuild from it
+    static constexpr bool CT = !(WIDE && DIM == 3);
+    static constexpr int NS = 2 * DIM + 3 + (CT ? 1 : 0);
     static constexpr int LO = WIDE ? 3 : 2;  // nodes below node i a face i+1/2 reads
     static constexpr int HI = WIDE ? 4 : 3;  // nodes above node i
     static constexpr int WIN = 4 + LO + HI;    // rows read by the four faces of an iteration
@@ -483,11 +594,12 @@ struct WgLds {
 // Stencil reads of face i+1/2 from the LDS ring: slot r (node i-3+r) is ring
 // row (b0 + r) mod RING.
 template <int DIM, int WIDE>
-struct LdsLoader {
+struct LdsLoader : StagedNodes<DIM, LdsLoader<DIM, WIDE>> {
     using W = WgLds<DIM, WIDE>;
     const W* L;
     unsigned la;  // byte offset of this lane in a ring row
     int b0;       // ring row of slot 0, in [0, RING)
+    double igm1;  // 1 / (gamma - 1)
 
     __device__ __forceinline__ LdsLoader after(double dep) const {
         LdsLoader c = *this;
@@ -495,18 +607,46 @@ struct LdsLoader {
         return c;
     }
 
-    __device__ __forceinline__ void slot(int r, double (&qv)[DIM + 2], double& V,
-                                         double (&s)[DIM]) const {
+    __device__ __forceinline__ double raw(int r, int v) const {
         int idx = b0 + r;
         idx = idx >= W::RING ? idx - W::RING : idx;
-        const char* row = reinterpret_cast<const char*>(&L->ring[idx][0][0]) + la;
+        return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(&L->ring[idx][0][0]) + la + v * 512);
+    }
+    __device__ __forceinline__ double at(int r, int v) const {
+        if constexpr (!W::CT) {
+            if (v == 2 * DIM + 3) return raw(r, DIM + 1);
+            if (v == DIM + 1) {
+                const double ct = raw(r, DIM + 1);
+                double k2 = 0.0;
 #pragma unroll
-        for (int v = 0; v < DIM + 2; ++v) qv[v] = *reinterpret_cast<const double*>(row + v * 512);
-        V = *reinterpret_cast<const double*>(row + (DIM + 2) * 512);
-#pragma unroll
-        for (int c = 0; c < DIM; ++c) s[c] = *reinterpret_cast<const double*>(row + (DIM + 3 + c) * 512);
+                for (int c = 0; c < DIM; ++c) k2 = fma(raw(r, 1 + c), raw(r, 1 + c), k2);
+                return fma(0.5, k2, ct * fabs(ct) * igm1);
+            }
+        }
+        return raw(r, v);
     }
 };
+
+// Primitives of one ring row in place of its conserved state (a wave, one
+// line per lane; the row's DMA must have landed).
+template <int DIM, int WIDE>
+__device__ __forceinline__ void wg_convert(WgLds<DIM, WIDE>& L, int slot, double gm1) {
+    constexpr int NV = DIM + 2;
+    const int lane = threadIdx.x & 63;
+    double q[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) q[v] = L.ring[slot][v][lane];
+    Prim<DIM> P;
+    to_prim<DIM>(q, gm1, P);
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) L.ring[slot][1 + c][lane] = P.u[c];
+    if constexpr (WgLds<DIM, WIDE>::CT) {
+        L.ring[slot][NV - 1][lane] = P.e;
+        L.ring[slot][2 * DIM + 3][lane] = P.ct;
+    } else {
+        L.ring[slot][NV - 1][lane] = P.ct;
+    }
+}
 
 // eta / zeta sweeps: a workgroup of four waves owns 64 grid lines along DIR
 // (consecutive in the flattened (i, other) index, so row loads are
@@ -516,8 +656,13 @@ struct LdsLoader {
 // per wave per iteration, prefetched one iteration ahead.  Per iteration
 // wave w evaluates the face f+1/2, f = k0 - 1 + 4 it + w, on its 64 lines
 // from the ring, the fluxes go to LDS and wave w forms node f's difference
-// F'_{f+1/2} - F'_{f-1/2}.  Every thread of the workgroup runs the same
-// iterations and barriers.  A caller that reuses `L` for another item must
+// F'_{f+1/2} - F'_{f-1/2}.  Each wave turns its row into primitives once its
+// DMA has landed, before the barrier that publishes it.  Bound by vector
+// issue.  With the primitives formed per node instead of per face, and no
+// wait for stores between the barriers, an RK3 step of a 256^3 block took
+// 9.25 ms against 9.85 in FP64 WENO5 (three sweeps per stage), 8.08 against
+// 8.29 FP32-mixed, and one of 128^3 with LU5 0.77 against 0.87.  Every thread
+// of the workgroup runs the same iterations and barriers.  A caller that reuses `L` for another item must
 // synchronise the workgroup first.
 template <int DIM, int DIR, int RECON, int Y, int PREC>
 __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
@@ -558,10 +703,11 @@ __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
     const int iters = (k1 - k0 + 1 + 3) / 4;  // faces k0-1/2 .. k1-1/2
     const int tb = k0 - 1 - W::LO;            // node index of ring row 0
     const int tmax = k1 - 1 + W::HI;          // last row any needed face reads
-    // a final epilogue takes node f's stage input and 1/J from its ring row
-    // (the stage input is the array this sweep reads, ep.qin == qs, and 1/J
-    // the metric array's last component, in every caller) instead of memory
-    constexpr bool own_qv = true;
+    const double gm1 = sk.gamma - 1.0;
+    // the stage input of the final epilogue: FP32 loads it with the other
+    // operands, FP64, which would spill, after the face (this workgroup's DMA
+    // read those lines an iteration or two before: L2 hits)
+    constexpr bool late_qin = sizeof(char_t<PREC>) == 8;
     auto load_row = [&](int t) {
         if (t > tmax) return;
         const int slot = (t - tb) % W::RING;
@@ -582,18 +728,19 @@ __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
     };
     for (int r = w; r < W::WIN; r += 4) load_row(tb + r);
     __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+    for (int r = w; r < W::WIN; r += 4)
+        if (tb + r <= tmax) wg_convert(L, r, gm1);
     __syncthreads();
     for (int it = 0; it < iters; ++it) {
         const int f = k0 - 1 + 4 * it + w;
         if (it + 1 < iters) load_row(tb + W::WIN + 4 * it + w);  // a row of the next iteration
         // this wave's node f: its epilogue operands load while the face is
-        // computed (in FP64 WENO the zeta sweep then spills a few registers,
-        // still faster than waiting for the loads after the face); 1/J and
-        // the stage input of node f are in its ring row already
+        // computed; 1/J is in its ring row already
         const bool mine = lane_ok && f >= k0 && f < k1;
         const long noff = lb + (long)f * G.sd[DIR];
         EpiPre<NV> pre;
-        if (mine) epi_load<NV>(ep, G.vol, noff, pre, own_qv);
+        if (mine) epi_load<NV>(ep, G.vol, noff, pre, !late_qin);
         double F[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) F[v] = 0.0;
@@ -602,40 +749,38 @@ __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
             ld.L = &L;
             ld.la = (unsigned)lane * 8u;
             ld.b0 = (f - 3 - tb + W::RING) % W::RING;
+            ld.igm1 = sk.igm1;
             face_flux<DIM, RECON, Y, char_t<PREC>>(ld, sk, F);
         }
 #pragma unroll
         for (int v = 0; v < NV; ++v) L.flux[w][v][lane] = F[v];
-        __syncthreads();
-        // FP32-mixed: the stores go after the second barrier, so that its
-        // wait does not hold for their completion (they complete while the
-        // next face is computed); FP64 stores before it, as holding the
-        // epilogue operands across the barrier would spill its registers
-        constexpr bool late_store = sizeof(char_t<PREC>) == 4;
-        double d[NV];
-        if (mine) {
-            const double* prev = w > 0 ? &L.flux[w - 1][0][0] : &L.carry[0][0];
+        // this wave's row of the next iteration, asked for before the face
+        __builtin_amdgcn_s_waitcnt(0);
+        asm volatile("" ::: "memory");
+        if (late_qin && mine) epi_load_qin<NV>(ep, G.vol, noff, pre);
+        if (it + 1 < iters && tb + W::WIN + 4 * it + w <= tmax)
+            wg_convert(L, (W::WIN + 4 * it + w) % W::RING, gm1);
+        // First barrier: the fluxes and the next iteration's rows are in LDS.
+        // Second: their readers are done, so that the next iteration may
+        // overwrite them.  Only those reads lie between the two; the epilogue
+        // and its stores follow, beside the next face.
+        lds_barrier();
+        double prev[NV], V = 0.0;
 #pragma unroll
-            for (int v = 0; v < NV; ++v) d[v] = F[v] - prev[v * 64 + lane];
-            if (own_qv && ep.mode >= EPI_LAST_RES) {
-                // node f's ring row (not overwritten before the next
-                // iteration's barrier: the prefetched rows take other slots)
-                const int slot = (f - tb) % W::RING;
-                pre.V = L.ring[slot][NV][lane];
-#pragma unroll
-                for (int v = 0; v < NV; ++v) pre.qin[v] = L.ring[slot][v][lane];
-            }
-            if (!late_store) epi_store<NV>(ep, G.vol, noff, pre, d);
-        }
-        __builtin_amdgcn_s_waitcnt(0);  // this wave's row DMA has landed
-        __syncthreads();                // every row of the next iteration is in LDS
-        // the next iteration's first face needs this iteration's last flux;
-        // the barrier above ended every read of the carry
-        if (w == 3) {
+        for (int v = 0; v < NV; ++v) prev[v] = (w > 0 ? &L.flux[w - 1][0][0] : &L.carry[0][0])[v * 64 + lane];
+        if (ep.mode >= EPI_LAST_RES) V = L.ring[(f - tb) % W::RING][NV][lane];
+        lds_barrier();
+        if (w == 3) {  // the next iteration's first face needs this one's last flux
 #pragma unroll
             for (int v = 0; v < NV; ++v) L.carry[v][lane] = F[v];
         }
-        if (late_store && mine) epi_store<NV>(ep, G.vol, noff, pre, d);
+        if (mine) {
+            double d[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) d[v] = F[v] - prev[v];
+            pre.V = V;
+            epi_store<NV>(ep, G.vol, noff, pre, d);
+        }
     }
 }
 
@@ -887,7 +1032,6 @@ __device__ __forceinline__ EpiK stage_epi(const BBlock& b, int stage, int mode, 
     e.stage0 = stage == 0;
     e.R = b.R;
     e.out = stage == 0 ? b.A : (stage == 1 ? b.B : b.q);
-    e.metV = b.met + (ndim == 3 ? 9 : 4) * b.G.vol;
     e.qin = stage_in(b, stage);
     e.qn = b.q;
     e.dt = b.dt;
@@ -915,25 +1059,30 @@ __global__ __launch_bounds__(256) FP_XSWEEP_ATTR(PREC, RECON, Y) void kb_sweep_x
     long item = (long)blockIdx.x * 4 + wave_id();
     int cur = 0;
     int b = 0;
-    if (item < total) {
-        b = find_block(st, nblk, item);
+    if (item >= total) return;
+    b = find_block(st, nblk, item);
+    XItem it;
+    {
         const BBlock& B = t_blk[ord[b]];
-        x_stage<DIM, NE>(B.G, B.met, stage_in(B, stage), item - st[b], x_window(B.G.n[0], NE), L.b[0]);
+        it = x_item<NE>(B.G, item - st[b], x_window(B.G.n[0], NE));
+        x_stage<DIM, NE>(B.G, B.met, stage_in(B, stage), it, L.b[0]);
     }
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
     for (; item < total; item += nw, cur ^= 1) {
-        __builtin_amdgcn_s_waitcnt(0);
-        asm volatile("" ::: "memory");
         int bn = b;
+        XItem next = it;
         if (item + nw < total) {
             bn = advance_block(st, nblk, b, item + nw);
             const BBlock& N = t_blk[ord[bn]];
-            x_stage<DIM, NE>(N.G, N.met, stage_in(N, stage), item + nw - st[bn], x_window(N.G.n[0], NE),
-                             L.b[cur ^ 1]);
+            next = x_item<NE>(N.G, item + nw - st[bn], x_window(N.G.n[0], NE));
+            x_stage<DIM, NE>(N.G, N.met, stage_in(N, stage), next, L.b[cur ^ 1]);
         }
         const BBlock& B = t_blk[ord[b]];
         const EpiK ep = stage_epi(B, stage, EPI_FIRST, DIM);
-        x_compute<DIM, RECON, Y, PREC, false>(B.G, sk, ep, item - st[b], x_window(B.G.n[0], NE), L.b[cur]);
+        x_compute<DIM, RECON, Y, PREC, false>(B.G, sk, ep, it, L.b[cur], L.ct);
         b = bn;
+        it = next;
     }
 }
 
@@ -982,7 +1131,7 @@ __global__ __launch_bounds__(256) FP_SWEEP_ATTR void k_face_flux(GeoK G, SchemeK
 #pragma unroll
     for (int d = 0; d < 3; ++d)
         if (d != DIR) lb += (long)c[d] * G.sd[d];
-    const LineLoader<DIM, DIR> ld(G, met, qs, lb, c[DIR] - 1);
+    const LineLoader<DIM, DIR> ld(G, met, qs, lb, c[DIR] - 1, sk.gamma);
     double fl[NV];
     face_flux<DIM, RECON, Y, char_t<PREC>>(ld, sk, fl);
 #pragma unroll
