@@ -150,6 +150,9 @@ GeoK make_geo(const fp_grid* g) {
     G.sd[2] = N0 * N1;
     G.vol = N0 * N1 * N2;
     G.base = G.g + G.g * N0 + (nd == 3 ? (long)G.g * N0 * N1 : 0);
+    G.xw = 0;
+    G.inv_nf = 1.0f / (float)(G.n[0] + 1);
+    G.inv_ne = 1.0f / (float)(G.n[0] + 8);
     return G;
 }
 
@@ -605,8 +608,10 @@ void build_tables(const fp_batch* b, const std::vector<fp_block>& blocks, const 
             B.S[2] = ndim == 3 ? seg_len(B.G.n[2], b->seg[2]) : 0;
             bool frozen = false;
             for (int d = 0; d < ndim; ++d) frozen = frozen || fb.grid.bc[d] == FP_BC_FROZEN;
+            const int ne = x_entries(b->sch.precision, b->sch.recon, b->sch.metric_order);
+            B.G.xw = x_window(B.G.n[0], ne);
             long items[BK_KINDS];
-            items[BK_X] = sweep_x_items(B.G.n, x_entries(b->sch.precision, b->sch.recon, b->sch.metric_order));
+            items[BK_X] = sweep_x_items(B.G.n, ne);
             items[BK_ETA] = sweep_wg_items(B.G.n, 1, B.S[1]);
             items[BK_ZETA] = ndim == 3 ? sweep_wg_items(B.G.n, 2, B.S[2]) : 0;
             items[BK_GHOST] = frozen ? (frozen_slab_nodes(B.G, ndim) + 255) / 256 : 0;

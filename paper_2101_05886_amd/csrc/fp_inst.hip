@@ -82,8 +82,10 @@ void launch_x_mode(const SweepArgs& a, const EpiK& ep, hipStream_t s) {
     static const int res = resident(&k_sweep_x<DIM, R, Y, P, ACC>);
     const long items = sweep_x_items(a.G.n, x_entries(P, R, Y));
     const long wgs = (items + 3) / 4;
+    GeoK G = a.G;
+    G.xw = x_window(G.n[0], x_entries(P, R, Y));
     hipLaunchKernelGGL((k_sweep_x<DIM, R, Y, P, ACC>), dim3((unsigned)(wgs < res ? wgs : res)), dim3(256), 0,
-                       s, a.G, a.sk, a.met, a.qs, ep);
+                       s, G, a.sk, a.met, a.qs, ep);
 }
 
 // the xi sweep writes the accumulator (FIRST), or adds to it after the
