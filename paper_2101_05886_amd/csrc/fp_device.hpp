@@ -207,39 +207,66 @@ __device__ __forceinline__ float weno5(float a, float b, float c, float d, float
     return num * fast_rcp(den);
 }
 
+// The reconstructions below take twice the split values; their indicators
+// are quadratic, so eps enters scaled and the weights are those of the split
+// values (powers of two: exact), the result twice their reconstruction.
+//
+// Indicators and weights see the window through its first differences f_j.
+// The candidates do too in FP64 (relative to the value beside the face, which
+// comes back at the end), but use the values themselves in FP32: the
+// reference subtraction leaves values near zero there, and rounding the
+// larger differences would cost accuracy.
+//
+// FP64 forms the weights over one common denominator, so that a
+// reconstruction takes two reciprocals (each a quarter-rate instruction and
+// four Newton operations) instead of five or six.  The products span up to
+// 1e-300 .. 1e300: eps is floored far below any indicator of rounding noise.
+// FP32 has no such range and takes a reciprocal per indicator.
+// RK3 steps with the indicators in values and a reciprocal each, and now:
+// FP64 WENOCU6 145x113x97 1.55 and 1.30 ms (2,248 and 1,914 FP64 operations
+// per face), FP32-mixed WENO7-M8 191x161x133 2.84 and 2.65 ms.
+
+// one indicator of WENO7: a quadratic form in three consecutive differences
+template <typename T>
+__device__ __forceinline__ T form3(T f1, T f2, T f3, T c11, T c12, T c13, T c22, T c23, T c33, T eps) {
+    return f1 * (c11 * f1 + c12 * f2 + c13 * f3) + (f2 * (c22 * f2 + c23 * f3) + (c33 * f3 * f3 + eps));
+}
+
 // WENO7-JS of a 7-point window v[0..6] (face between v[3] and v[4], upwind
 // side v[0]): four cubic candidates, optimal weights (1, 12, 18, 4)/35,
 // smoothness indicators as the integer quadratic forms (240 x the Jiang-Shu
-// measure), weights C_k/(beta_k+eps)^2 from reciprocals (the indicators can
-// be large, so no common-denominator products).  Called on twice the split
-// values with 4 eps, it returns twice their reconstruction (the indicators
-// are quadratic: exact).
+// measure; in differences their coefficients are a quarter to a half as
+// large), weights C_k/(beta_k+eps)^2.  Takes 4 eps.
 template <typename T>
 __device__ __forceinline__ T weno7(const T (&v)[7], T eps) {
     const T a = v[0], b = v[1], c = v[2], d = v[3], e = v[4], f = v[5], g = v[6];
-    const T q0 = T(-3) * a + T(13) * b - T(23) * c + T(25) * d;
-    const T q1 = b - T(5) * c + T(13) * d + T(3) * e;
-    const T q2 = -c + T(7) * d + T(7) * e - f;
-    const T q3 = T(3) * d + T(13) * e - T(5) * f + g;
-    T b0 = a * (T(547) * a - T(3882) * b + T(4642) * c - T(1854) * d) +
-           b * (T(7043) * b - T(17246) * c + T(7042) * d) + c * (T(11003) * c - T(9402) * d) +
-           T(2107) * d * d;
-    T b1 = b * (T(267) * b - T(1642) * c + T(1602) * d - T(494) * e) +
-           c * (T(2843) * c - T(5966) * d + T(1922) * e) + d * (T(3443) * d - T(2522) * e) +
-           T(547) * e * e;
-    T b2 = c * (T(547) * c - T(2522) * d + T(1922) * e - T(494) * f) +
-           d * (T(3443) * d - T(5966) * e + T(1602) * f) + e * (T(2843) * e - T(1642) * f) +
-           T(267) * f * f;
-    T b3 = d * (T(2107) * d - T(9402) * e + T(7042) * f - T(1854) * g) +
-           e * (T(11003) * e - T(17246) * f + T(4642) * g) + f * (T(7043) * f - T(3882) * g) +
-           T(547) * g * g;
-    b0 += eps;
-    b1 += eps;
-    b2 += eps;
-    b3 += eps;
-    const T a0 = T(1) * rcp<T>(b0 * b0), a1 = T(12) * rcp<T>(b1 * b1);
-    const T a2 = T(18) * rcp<T>(b2 * b2), a3 = T(4) * rcp<T>(b3 * b3);
-    return (a0 * q0 + a1 * q1 + a2 * q2 + a3 * q3) * rcp<T>(T(12) * (a0 + a1 + a2 + a3));
+    const T f0 = b - a, f1 = c - b, f2 = d - c, f3 = e - d, f4 = f - e, f5 = g - f;
+    constexpr bool F64 = sizeof(T) == 8;
+    const T ep = F64 ? fmax(eps, T(1e-50)) : eps;
+    T b0 = form3<T>(f0, f1, f2, T(547), T(-2788), T(1854), T(3708), T(-5188), T(2107), ep);
+    T b1 = form3<T>(f1, f2, f3, T(267), T(-1108), T(494), T(1468), T(-1428), T(547), ep);
+    T b2 = form3<T>(f2, f3, f4, T(547), T(-1428), T(494), T(1468), T(-1108), T(267), ep);
+    T b3 = form3<T>(f3, f4, f5, T(2107), T(-5188), T(1854), T(3708), T(-2788), T(547), ep);
+    b0 *= b0;
+    b1 *= b1;
+    b2 *= b2;
+    b3 *= b3;
+    if constexpr (F64) {
+        const T b01 = b0 * b1, b23 = b2 * b3;
+        const T a0 = b1 * b23, a1 = b0 * (T(12) * b23), a2 = b3 * (T(18) * b01), a3 = b2 * (T(4) * b01);
+        const T q0 = T(3) * f0 - T(10) * f1 + T(13) * f2;  // 12 (q_k - d)
+        const T q1 = T(4) * f2 + T(3) * f3 - f1;
+        const T q2 = T(6) * f3 + f2 - f4;
+        const T q3 = T(9) * f3 - T(4) * f4 + f5;
+        return fma(a0 * q0 + a1 * q1 + a2 * q2 + a3 * q3, rcp<T>(T(12) * (a0 + a1 + a2 + a3)), d);
+    } else {
+        const T q0 = T(-3) * a + T(13) * b - T(23) * c + T(25) * d;
+        const T q1 = b - T(5) * c + T(13) * d + T(3) * e;
+        const T q2 = -c + T(7) * d + T(7) * e - f;
+        const T q3 = T(3) * d + T(13) * e - T(5) * f + g;
+        const T a0 = rcp<T>(b0), a1 = T(12) * rcp<T>(b1), a2 = T(18) * rcp<T>(b2), a3 = T(4) * rcp<T>(b3);
+        return (a0 * q0 + a1 * q1 + a2 * q2 + a3 * q3) * rcp<T>(T(12) * (a0 + a1 + a2 + a3));
+    }
 }
 
 // WENOCU6 (the adaptive central-upwind sixth-order WENO of Hu, Wang and Adams,
@@ -249,48 +276,63 @@ __device__ __forceinline__ T weno7(const T (&v)[7], T eps) {
 // sixth-order central interpolation).  The downwind slot's indicator is beta6,
 // the Jiang-Shu measure (derivative orders 1..5 over cell i) of the quintic
 // through all six cell averages, evaluated from the quintic's Taylor
-// coefficients D_l = p^(l) at the centre of cell i: each D_l is a difference
-// stencil (its coefficients sum to zero), so beta6 keeps its accuracy in FP32,
-// where the expanded integer quadratic form of the six values cancels to
-// noise.  Weights alpha_k = d_k (C + tau6/(beta_k + eps))^2, C = 20,
+// coefficients D_l = p^(l) at the centre of cell i, which are combinations of
+// the window's first to fifth differences (f, t, u; D4, D5 are the centred
+// fourth and the fifth difference): beta6 keeps its accuracy in FP32, where
+// the expanded integer quadratic form of the six values cancels to noise.
+// Every indicator is formed times four (4 beta_k = 13/3 t^2 + s^2), so this
+// takes 16 eps.  Weights alpha_k = d_k (C + tau6/(beta_k + eps))^2, C = 20,
 // tau6 = beta6 - (beta_0 + 4 beta_1 + beta_2)/6, evaluated as
 // ((C m + tau6 m/(beta_k+eps)) / (m + |tau6|))^2 with m = min_k (beta_k+eps):
-// the same ratios, every factor in [-C, C], so no overflow for any eps.
-// Called on twice the split values with 4 eps, it returns twice their
-// reconstruction (indicators and tau6 are quadratic: exact).
+// the same ratios, every factor in [-C, C].
 template <typename T>
 __device__ __forceinline__ T wenocu6(const T (&v)[6], T eps) {
     const T a = v[0], b = v[1], c = v[2], d = v[3], e = v[4], f = v[5];
-    const T q0 = T(2) * a - T(7) * b + T(11) * c;
-    const T q1 = -b + T(5) * c + T(2) * d;
-    const T q2 = T(2) * c + T(5) * d - e;
-    const T q3 = T(11) * d - T(7) * e + T(2) * f;
-    const T t0 = a - T(2) * b + c, s0 = a - T(4) * b + T(3) * c;
-    const T t1 = b - T(2) * c + d, s1 = d - b;
-    const T t2 = c - T(2) * d + e, s2 = T(3) * c - T(4) * d + e;
-    const T k13 = T(13.0 / 12.0);
-    const T b0 = k13 * t0 * t0 + T(0.25) * s0 * s0;
-    const T b1 = k13 * t1 * t1 + T(0.25) * s1 * s1;
-    const T b2 = k13 * t2 * t2 + T(0.25) * s2 * s2;
-    const T D1 = (T(341) * a - T(2785) * b - T(2590) * c + T(6670) * d - T(1895) * e + T(259) * f) *
-                 T(1.0 / 5760.0);
-    const T D2 = (-a + T(12) * b - T(22) * c + T(12) * d - e) * T(0.125);
-    const T D3 = (T(-5) * a - T(11) * b + T(70) * c - T(94) * d + T(47) * e - T(7) * f) * T(1.0 / 24.0);
-    const T D4 = a - T(4) * b + T(6) * c - T(4) * d + e;
-    const T D5 = -a + T(5) * b - T(10) * c + T(10) * d - T(5) * e + f;
-    const T b6 = D1 * (D1 + D3 * T(1.0 / 12.0) + D5 * T(1.0 / 960.0)) +
-                 D2 * (D2 * T(13.0 / 12.0) + D4 * T(7.0 / 80.0)) +
-                 D3 * (D3 * T(1043.0 / 960.0) + D5 * T(4709.0 / 53760.0)) +
-                 D4 * D4 * T(87617.0 / 80640.0) + D5 * D5 * T(50467427.0 / 46448640.0);
+    const T f1 = b - a, f2 = c - b, f3 = d - c, f4 = e - d, f5 = f - e;
+    const T t0 = f2 - f1, t1 = f3 - f2, t2 = f4 - f3, t3 = f5 - f4;
+    const T u1 = t1 - t0, u2 = t2 - t1, u3 = t3 - t2;
+    const T s0 = T(3) * f2 - f1, s1 = f2 + f3, s2 = T(3) * f3 - f4;
+    const T k13 = T(13.0 / 3.0);
+    constexpr bool F64 = sizeof(T) == 8;
+    const T ep = F64 ? fmax(eps, T(1e-60)) : eps;
+    const T b0 = k13 * t0 * t0 + s0 * s0;
+    const T b1 = k13 * t1 * t1 + s1 * s1;
+    const T b2 = k13 * t2 * t2 + s2 * s2;
+    const T D4 = u2 - u1, D5 = (u3 - u2) - D4;
+    const T G1 = s1 - T(341.0 / 2880.0) * u1 - T(1118.0 / 2880.0) * u2 + T(259.0 / 2880.0) * u3;  // 2 D1
+    const T G2 = T(2) * t1 - T(0.25) * D4;                                                          // 2 D2
+    const T G3 = T(5.0 / 12.0) * u1 + T(26.0 / 12.0) * u2 - T(7.0 / 12.0) * u3;                     // 2 D3
+    const T b6 = G1 * (G1 + G3 * T(1.0 / 12.0) + D5 * T(1.0 / 480.0)) +
+                 G2 * (G2 * T(13.0 / 12.0) + D4 * T(7.0 / 40.0)) +
+                 G3 * (G3 * T(1043.0 / 960.0) + D5 * T(4709.0 / 26880.0)) +
+                 D4 * D4 * T(87617.0 / 20160.0) + D5 * D5 * T(50467427.0 / 11612160.0);
     const T tau = b6 - (b0 + T(4) * b1 + b2) * T(1.0 / 6.0);
-    const T e0 = b0 + eps, e1 = b1 + eps, e2 = b2 + eps, e3 = b6 + eps;
+    const T e0 = b0 + ep, e1 = b1 + ep, e2 = b2 + ep, e3 = b6 + ep;
     const T m = fmin(fmin(e0, e1), fmin(e2, e3));
-    const T ig = rcp<T>(m + fabs(tau));
-    const T sC = T(20) * (m * ig), st = tau * ig;
-    const T w0 = sC + st * (m * rcp<T>(e0)), w1 = sC + st * (m * rcp<T>(e1));
-    const T w2 = sC + st * (m * rcp<T>(e2)), w3 = sC + st * (m * rcp<T>(e3));
-    const T a0 = w0 * w0, a1 = T(9) * (w1 * w1), a2 = T(9) * (w2 * w2), a3 = w3 * w3;
-    return (a0 * q0 + a1 * q1 + a2 * q2 + a3 * q3) * rcp<T>(T(6) * (a0 + a1 + a2 + a3));
+    const T mt = m + fabs(tau);
+    if constexpr (F64) {
+        const T e01 = e0 * e1, e23 = e2 * e3, P = e01 * e23;
+        const T R = rcp<T>(P * mt), ig = P * R;  // 1/(m + |tau|)
+        const T sC = T(20) * (m * ig);
+        const T x = tau * m * ig * (mt * R);  // tau m / ((m + |tau|) e0 e1 e2 e3)
+        const T x01 = x * e23, x23 = x * e01;
+        const T w0 = fma(x01, e1, sC), w1 = fma(x01, e0, sC), w2 = fma(x23, e3, sC), w3 = fma(x23, e2, sC);
+        const T a0 = w0 * w0, a1 = T(9) * (w1 * w1), a2 = T(9) * (w2 * w2), a3 = w3 * w3;
+        const T q0 = T(5) * f2 - T(2) * f1, q1 = T(2) * f3 + f2;  // 6 (q_k - c)
+        const T q2 = T(4) * f3 - f4, q3 = T(6) * f3 - T(5) * f4 + T(2) * f5;
+        return fma(a0 * q0 + a1 * q1 + a2 * q2 + a3 * q3, rcp<T>(T(6) * (a0 + a1 + a2 + a3)), c);
+    } else {
+        const T ig = rcp<T>(mt);
+        const T sC = T(20) * (m * ig), st = tau * ig;
+        const T w0 = sC + st * (m * rcp<T>(e0)), w1 = sC + st * (m * rcp<T>(e1));
+        const T w2 = sC + st * (m * rcp<T>(e2)), w3 = sC + st * (m * rcp<T>(e3));
+        const T a0 = w0 * w0, a1 = T(9) * (w1 * w1), a2 = T(9) * (w2 * w2), a3 = w3 * w3;
+        const T q0 = T(2) * a - T(7) * b + T(11) * c;
+        const T q1 = -b + T(5) * c + T(2) * d;
+        const T q2 = T(2) * c + T(5) * d - e;
+        const T q3 = T(11) * d - T(7) * e + T(2) * f;
+        return (a0 * q0 + a1 * q1 + a2 * q2 + a3 * q3) * rcp<T>(T(6) * (a0 + a1 + a2 + a3));
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -565,10 +607,10 @@ __device__ __forceinline__ void face_flux_weno(const LD& ld, const SchemeK& sk,
     // WENOCU6's eps may be far below the FP32 normal range (1e-40 in the
     // published scheme): the FP32 path floors it at 1e-30.  The
     // reconstructions take twice the split values a +- lambda b (the split's
-    // 1/2 goes on the back-projected sum), so WENOCU6 takes 4 eps and WENO5,
-    // whose indicators are also scaled by 4, 16 eps.
+    // 1/2 goes on the back-projected sum) and scale their indicators by 4:
+    // 16 eps.
     const T eps = (CU6 && sizeof(T) == 4) ? fmax(T(sk.eps), T(1e-30)) : T(sk.eps);
-    const T epsw = CU6 ? T(4) * eps : T(16) * eps;
+    const T epsw = T(16) * eps;
     T h[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
