@@ -270,7 +270,9 @@ fp_status fp_solve_bcs(const fp_grid *grid, const fp_scheme *scheme, const fp_bc
                        int64_t nsteps, void *stream);
 
 /* Instrumented step (a measurement aid; none of the paper's operations is
- * added): one RK3 step of q (Sec. 2.2) exactly as fp_rk3_step launches it,
+ * added): one RK3 step of q (Sec. 2.2), bitwise that of fp_rk3_step and with
+ * its launches (except that the xi and eta sweeps of a small 2D block, which
+ * fp_rk3_step runs in one launch, are launched and timed apart),
  * with the boundary faces of fp_solve_bcs at the stage times of a step from
  * t when bcs is non-NULL, and with the viscous part of fp_solve_ns when
  * scheme->mu > 0 (vwork then required, else ignored), and a HIP event

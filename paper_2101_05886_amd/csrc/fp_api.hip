@@ -186,32 +186,38 @@ SchemeK make_sk(const fp_scheme* s) {
     return k;
 }
 
-// Segments of the eta / zeta sweeps.  A workgroup owns 64 lines and one
-// segment of S nodes, evaluating S+1 faces four at a time.  The plan
-// minimises (rounds of resident workgroups) x (iterations per workgroup),
-// with two resident workgroups per CU on 256 CUs.
+// Segment length (nodes per item) of a sweep along an axis of nd nodes with
+// `lblocks` blocks of 64 lines: an item of S nodes evaluates its S + 1 faces
+// four at a time.  The plan minimises (rounds of resident workgroups, two on
+// each of 256 CUs) x (iterations + 1/2 per workgroup): filling the ring costs
+// an item about half an iteration.  S = 3, one iteration, is the shortest,
+// and the best for blocks too small to fill the chip (a 45x33x29 residual:
+// 30.2 us with S = 4, two iterations, 24.0 with 3).
+int plan_segment(int nd, long lblocks) {
+    const long resident = 512;
+    long best = -1;
+    int bestS = nd;
+    for (int ns = 1; ns <= nd; ++ns) {
+        const int S = (nd + ns - 1) / ns;
+        if (S < 3 && ns > 1) break;
+        const long segs = (nd + S - 1) / S;
+        const long iters = (S + 4) / 4;
+        const long rounds = (lblocks * segs + resident - 1) / resident;
+        const long cost = rounds * (2 * iters + 1);
+        if (best < 0 || cost < best) {
+            best = cost;
+            bestS = S;
+        }
+    }
+    return bestS;
+}
+
 void plan_segments(const GeoK& G, int ndim, SweepArgs& a) {
-    const long resident = 256L * 2;
     for (int d = 1; d < ndim; ++d) {
         const int oth = d == 1 ? 2 : 1;
         const long lblocks = ((long)G.n[0] * G.n[oth] + 63) / 64;
-        const int nd = G.n[d];
-        long best = -1;
-        int bestS = nd;
-        for (int ns = 1; ns <= nd; ++ns) {
-            const int S = (nd + ns - 1) / ns;
-            if (S < 4 && ns > 1) break;
-            const long segs = (nd + S - 1) / S;
-            const long iters = (S + 1 + 3) / 4;
-            const long rounds = (lblocks * segs + resident - 1) / resident;
-            const long cost = rounds * iters;
-            if (best < 0 || cost < best) {
-                best = cost;
-                bestS = S;
-            }
-        }
-        a.S[d] = bestS;
-        a.nseg[d] = (nd + bestS - 1) / bestS;
+        a.S[d] = plan_segment(G.n[d], lblocks);
+        a.nseg[d] = (G.n[d] + a.S[d] - 1) / a.S[d];
     }
     a.S[0] = a.nseg[0] = 0;
     if (ndim == 2) a.S[2] = a.nseg[2] = 0;
@@ -354,10 +360,12 @@ void launch_run_start(const Ctx& c, const double* q, double* work, hipStream_t s
 // input gets its ghost layers at the stage time t, t + dt, t + dt/2; with
 // global LF speeds, stage k reduces into the workspace tail's set k.
 // (tdev: the step's start time on the device, then the stage times are
-// *tdev + (0, dt, dt/2) and `t` is ignored)
+// *tdev + (0, dt, dt/2) and `t` is ignored; it is advanced by the step, by
+// the last stage's speed reduction, which follows the last use, or by a
+// launch at the end)
 hipError_t run_rk3(const Ctx& c, const double* met, double* q, double* work, double dt, hipStream_t s,
                    const BcK* bc = nullptr, double t = 0.0, double* vwork = nullptr, bool ghosts = true,
-                   const double* tdev = nullptr, Probe* probe = nullptr) {
+                   double* tdev = nullptr, Probe* probe = nullptr) {
     const bool visc = c.sch.mu > 0.0;
     double* A = work;
     double* B = work + c.state_elems;
@@ -390,6 +398,10 @@ hipError_t run_rk3(const Ctx& c, const double* met, double* q, double* work, dou
             a.sk.glf = sets + kGlfSetStride * k;
             a.glf_next = sets + kGlfSetStride * ((k + 1) % 3);
             a.glf = 1;
+            if (tdev && k == 2) {
+                a.glf_time = tdev;
+                a.time_dt = dt;
+            }
         }
         a.met = met;
         a.qs = in[k];
@@ -400,6 +412,10 @@ hipError_t run_rk3(const Ctx& c, const double* met, double* q, double* work, dou
         plan_segments(c.G, c.grid.ndim, a);
         hipError_t err = c.stage(a, s);
         if (err != hipSuccess) return err;
+    }
+    if (tdev && !glf) {
+        hipLaunchKernelGGL(k_time_advance, dim3(1), dim3(64), 0, s, tdev, dt);
+        return hipGetLastError();
     }
     return hipSuccess;
 }
@@ -1069,10 +1085,6 @@ fp_status fp_solve_bcs(const fp_grid* g, const fp_scheme* sch, const fp_bcs* bcs
             e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
             if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
             hipError_t le = run_rk3(c, met, q, work, dt, cs, &k, 0.0, nullptr, false, T);
-            if (le == hipSuccess) {
-                hipLaunchKernelGGL(k_time_advance, dim3(1), dim3(64), 0, cs, T, dt);
-                le = hipGetLastError();
-            }
             hipGraph_t graph = nullptr;
             e = hipStreamEndCapture(cs, &graph);
             if (le != hipSuccess) {

@@ -39,6 +39,12 @@ struct GeoK {
     float inv_nf, inv_ne;  // 1 / (n0 + 1), 1 / (n0 + 8)
 };
 
+// Global Lax-Friedrichs speeds.  The speeds live in sets of three directions; direction d of a set takes
+// the three doubles at 16 d (one 128-byte line per direction, so the
+// reductions of different directions do not contend for one line).
+constexpr int kGlfDirStride = 16;
+constexpr int kGlfSetStride = 3 * kGlfDirStride;
+
 // What a sweep does with the flux difference d = F'_{i+1/2} - F'_{i-1/2} of
 // its direction at node `off`:
 //   FIRST: R = -d        MID: R = R - d
@@ -894,16 +900,195 @@ __global__ __launch_bounds__(256) FP_SWEEP_ATTR void k_sweep_wg(GeoK G, SchemeK 
 }
 
 // ---------------------------------------------------------------------------
+// both sweeps of a small 2D block in one launch
+// ---------------------------------------------------------------------------
+// A workgroup owns one row k of up to 56 nodes: wave 0 and 1 evaluate its
+// eta faces k -+ 1/2, wave 2 the xi faces along it, from the stencil rows
+// that all four waves stage in LDS (64 columns, four beyond the nodes on each
+// side); wave 2 then forms both flux differences and applies the final
+// epilogue, so the residual accumulator stays in registers.
+// Why: on a block of a few thousand nodes a launch lasts as long as one
+// chain of load, face and store, whatever its size, and this runs the two
+// directions side by side: 7.3 us per RK stage of a 64^2 WENO5 block, launch
+// gap included, against 13.9 for the two sweeps (and 10.2 for a workgroup
+// that marches along j over a ring of rows, which was tried first).  It
+// evaluates every eta face twice, so it pays while the chip has room.  The
+// face code, its inputs and the order of the sums are those of the two
+// sweeps: the results are bitwise theirs.
+constexpr int kRowNodes = 56;
+template <int WIDE>
+struct RowLds {
+    static constexpr int NC = 64;  // columns: x = i0 - 4 .. i0 + 59
+    static constexpr int LO = WIDE ? 3 : 2, HI = WIDE ? 4 : 3;
+    static constexpr int ROWS = 2 + LO + HI;  // nodes k - 1 - LO .. k + HI
+    static constexpr int NS = 8;              // rho, u, v, E/rho, 1/J, s_eta, thermal speed
+    double row[ROWS][NS][NC];
+    double sx[2][NC];        // s_xi of row k
+    double flux[2][4][NC];   // the two eta faces
+};
+
+// Stencil reads of a face of either direction (eta: wave-uniform): slot r is
+// row b0 + r, or column r of row k.
+template <int WIDE>
+struct RowLoader : StagedNodes<2, RowLoader<WIDE>> {
+    using W = RowLds<WIDE>;
+    const W* L;
+    unsigned la;  // byte offset of this lane's column
+    int b0;
+    bool eta;
+
+    __device__ __forceinline__ RowLoader after(double dep) const {
+        RowLoader c = *this;
+        asm volatile("" : "+v"(c.la) : "v"(dep));
+        return c;
+    }
+    __device__ __forceinline__ double at(int r, int v) const {
+        const bool s = v == 5 || v == 6;
+        const unsigned eo = (unsigned)(((b0 + r) * W::NS + v) * W::NC) * 8u;
+        const unsigned xo =
+            s ? (unsigned)(W::ROWS * W::NS + v - 5) * W::NC * 8u + (unsigned)r * 8u
+              : (unsigned)(((W::LO + 1) * W::NS + v) * W::NC + r) * 8u;
+        return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(L) + la + (eta ? eo : xo));
+    }
+};
+
+// One 2D residual evaluation with its final epilogue `ep` (MODE: EPI_LAST_RES
+// or EPI_LAST_RK); ACC: the accumulator holds the viscous part already.
+template <int RECON, int Y, int PREC, int MODE, bool ACC>
+__global__ __launch_bounds__(256) FP_SWEEP_ATTR void k_row_2d(GeoK G, SchemeK sk, const double* __restrict__ met,
+                                                              const double* qs, EpiK ep_, int ti) {
+    using W = RowLds<wide_stencil(RECON, Y)>;
+    constexpr int NV = 4;
+    __shared__ W L;
+    EpiK ep = ep_;
+    ep.mode = MODE;
+    const int lane = threadIdx.x & 63;
+    const int w = wave_id();
+    const int n0 = G.n[0], nd = G.n[1];
+    const int tiles = (n0 + ti - 1) / ti;
+    const int k = (int)(blockIdx.x / (unsigned)tiles);
+    const int i0 = (int)(blockIdx.x % (unsigned)tiles) * ti, tw = min(ti, n0 - i0);  // nodes i0 .. i0 + tw - 1
+    const long vol = G.vol;
+    const int sd1 = (int)G.sd[1];
+    const double gm1 = sk.gamma - 1.0;
+    // DMA: lane l moves dword (l & 1) of column 32 p + l / 2 of a row.  The
+    // state's columns wrap on a periodic axis; columns past the stored ghosts
+    // (never read) repeat the last.
+    unsigned cq[2], cm[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int x = i0 - 4 + 32 * p + (lane >> 1);
+        const int xm = min(max(x, -G.g), n0 - 1 + G.g);
+        int xq = xm;
+        if (G.bc[0] == 0) {
+            xq = x < 0 ? x + n0 : (x >= n0 ? x - n0 : x);
+            xq = min(max(xq, 0), n0 - 1);
+        }
+        cq[p] = (unsigned)(G.base + xq) * 8u + (unsigned)(lane & 1) * 4u;
+        cm[p] = (unsigned)(G.base + xm) * 8u + (unsigned)(lane & 1) * 4u;
+    }
+    for (int r = w; r < W::ROWS; r += 4) {
+        const int t = k - 1 - W::LO + r;
+        int tt = t;
+        if (G.bc[1] == 0) tt = t < 0 ? t + nd : (t >= nd ? t - nd : t);
+        const unsigned qo = (unsigned)(tt * sd1) * 8u, mo = (unsigned)(t * sd1) * 8u;
+        const double* qp = rebase(qs);
+        const double* mp = rebase(met);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) dma_dword(qp + v * vol, vol, &L.row[r][v][32 * p], cq[p] + qo);
+            dma_dword(mp + 4 * vol, vol, &L.row[r][4][32 * p], cm[p] + mo);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) dma_dword(mp + (2 + c) * vol, vol, &L.row[r][5 + c][32 * p], cm[p] + mo);
+            if (t == k) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) dma_dword(mp + c * vol, vol, &L.sx[c][32 * p], cm[p] + mo);
+            }
+        }
+    }
+    // wave 2, lane l >= 1, owns the node of column l - 1 of the tile, to the
+    // right of its left face
+    const bool mine = w == 2 && lane >= 1 && lane <= tw;
+    const unsigned noff = (unsigned)(G.base + i0 + lane - 1 + k * sd1);
+    EpiPre<NV> pre;
+    if (mine) {
+        if (ACC) {
+            const double* R = rebase(ep.R);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) pre.R[v] = ldb(R + v * vol, vol, noff * 8u);
+        }
+        if (MODE == EPI_LAST_RK) {
+            epi_load_qin<NV>(ep, vol, noff, pre);
+            if (!ep.stage0) {
+                const double* qn = rebase(ep.qn);
+#pragma unroll
+                for (int v = 0; v < NV; ++v) pre.qn[v] = ldb(qn + v * vol, vol, noff * 8u);
+            }
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+    for (int r = w; r < W::ROWS; r += 4) {  // each wave converts the rows it brought
+        double q[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) q[v] = L.row[r][v][lane];
+        Prim<2> P;
+        to_prim<2>(q, gm1, P);
+        L.row[r][1][lane] = P.u[0];
+        L.row[r][2][lane] = P.u[1];
+        L.row[r][3][lane] = P.e;
+        L.row[r][7][lane] = P.ct;
+    }
+    lds_barrier();
+    double F[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) F[v] = 0.0;
+    const bool eta = w < 2;
+    if (w < 3 && (eta ? lane < tw : lane <= tw)) {
+        RowLoader<wide_stencil(RECON, Y)> ld;
+        ld.L = &L;
+        ld.eta = eta;
+        ld.la = (unsigned)(eta ? lane + 4 : lane) * 8u;
+        ld.b0 = w - 3 + W::LO;  // face k - 1 + w + 1/2: slot r is node k - 1 + w - 3 + r
+        SchemeK kd = sk;
+        if (eta) kd.glf += kGlfDirStride;  // the direction's speeds
+        face_flux<2, RECON, Y, char_t<PREC>>(ld, kd, F);
+    }
+    if (eta) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) L.flux[w][v][lane] = F[v];
+    }
+    double d[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) d[v] = F[v] - __shfl_up(F[v], 1, 64);
+    lds_barrier();
+    if (mine) {
+        double dy[NV];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            dy[v] = L.flux[1][v][lane - 1] - L.flux[0][v][lane - 1];
+            pre.R[v] = ACC ? pre.R[v] - d[v] : -d[v];
+        }
+        pre.V = L.row[W::LO + 1][4][lane + 3];
+        epi_store<NV>(ep, vol, noff, pre, dy);
+    }
+}
+
+// Workgroups of the kernel above, and whether it takes the block: two rounds
+// of the two that a CU holds.  WENO5 FP64, us per stage, against the two
+// sweeps: 110^2 (220 workgroups) 7.5 and 14.2, 160^2 (480) 10.2 and 14.6,
+// 224^2 (896) 15.8 and 17.3, 30x1000 (1000) 16.2 and 17.0, 256^2 (1280) 19.1
+// and 19.3, 300^2 (1800) 26.9 and 20.3.
+inline long row_2d_blocks(const int n[3]) { return (long)((n[0] + kRowNodes - 1) / kRowNodes) * n[1]; }
+inline bool row_2d_fits(const int n[3]) { return row_2d_blocks(n) <= 1024; }
+
+// ---------------------------------------------------------------------------
 // global Lax-Friedrichs speeds
 // ---------------------------------------------------------------------------
 
-// The speeds live in sets of three directions; direction d of a set takes
-// the three doubles at 16 d (one 128-byte line per direction, so the
-// reductions of different directions do not contend for one line).
-constexpr int kGlfDirStride = 16;
-constexpr int kGlfSetStride = 3 * kGlfDirStride;
 // faces per thread of the reduction (neighbours along the face direction)
-constexpr int kGlfSeg = 2;
+constexpr int kGlfSeg = 4;
 
 // Zero one speed set (a template: this header is compiled into several objects).
 template <int DIM>
@@ -911,20 +1096,27 @@ __global__ void k_glf_reset(unsigned long long* set) {
     if (threadIdx.x < 9) set[kGlfDirStride * (threadIdx.x / 3) + threadIdx.x % 3] = 0ull;
 }
 
+// The time of a captured step sequence, T = {t, t0, steps}: set before the
+// replays; at the end of every step steps += 1 and t = t0 + steps dt (the
+// step start times of an uncaptured run, without accumulated rounding).
+__device__ __forceinline__ void time_advance(double* T, double dt) {
+    const double n = T[2] + 1.0;
+    T[2] = n;
+    T[0] = T[1] + n * dt;
+}
+
 // velocity and sound speed of the node at `off`
 template <int DIM>
-__device__ __forceinline__ void glf_node(const double* __restrict__ q, long vol, long off, double gamma,
+__device__ __forceinline__ void glf_node(const double* __restrict__ q, long vol, long off, double gm1, double sg,
                                          double* u, double& cs) {
-    const double rho = q[off];
-    double k2 = 0.0;
+    double qv[DIM + 2];
 #pragma unroll
-    for (int c = 0; c < DIM; ++c) {
-        const double mc = q[(1 + c) * vol + off];
-        u[c] = mc / rho;
-        k2 += mc * u[c];
-    }
-    const double p = (gamma - 1.0) * (q[(DIM + 1) * vol + off] - 0.5 * k2);
-    cs = sqrt(gamma * p / rho);
+    for (int v = 0; v < DIM + 2; ++v) qv[v] = q[v * vol + off];
+    Prim<DIM> P;
+    to_prim<DIM>(qv, gm1, P);
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) u[c] = P.u[c];
+    cs = sg * fmax(P.ct, 0.0);
 }
 
 // The largest local Lax-Friedrichs speed over every face of every direction
@@ -943,17 +1135,23 @@ __device__ __forceinline__ void glf_node(const double* __restrict__ q, long vol,
 // memory) for eta and zeta.  Each block reduces its maxima and folds them
 // into `set` with one integer atomic max per class (non-negative doubles
 // order as their bit patterns do): few large blocks, since atomics on one
-// cache line serialise.  Block 0 also zeroes `next` (the set the following
-// reduction folds into; NULL: none).
+// cache line serialise.  Four faces a thread evaluate 2.25 nodes per face
+// (two faces: 3.5); with the primitives of the sweeps in place of divisions,
+// 14.0 us against 15.1 on a 961x241 grid, where launch, load latency and the
+// atomics are the rest.  Block 0 also zeroes `next` (the set the following
+// reduction folds into; NULL: none) and, in the last stage of a captured
+// step, advances the device time `T` that the next step starts from (NULL:
+// none; a launch of its own took 4 us of a 190 us step).
 template <int DIM, int Y, int LO>
-__global__ __launch_bounds__(1024) void k_glf(GeoK G, double gamma, const double* __restrict__ met,
+__global__ __launch_bounds__(512) void k_glf(GeoK G, double gm1, double sg, const double* __restrict__ met,
                                               const double* __restrict__ q, unsigned long long* set,
-                                              unsigned long long* next, int bpd) {
+                                              unsigned long long* next, int bpd, double* T, double dt) {
     constexpr int NMET = DIM == 3 ? 10 : 5;
     constexpr int NW = kGlfSeg + 2 * LO + 1;  // stencil nodes of one segment
     const int d = blockIdx.x / bpd, bb = blockIdx.x % bpd;
     if (next && blockIdx.x == 0 && threadIdx.x < 9)
         next[kGlfDirStride * (threadIdx.x / 3) + threadIdx.x % 3] = 0ull;
+    if (T && blockIdx.x == 0 && threadIdx.x == 0) time_advance(T, dt);
     const int e1 = d == 0 ? 1 : 0, e2 = d == 2 ? 1 : 2;
     const long n1 = G.n[e1], n12 = n1 * G.n[e2];
     const int nd = G.n[d];
@@ -964,15 +1162,15 @@ __global__ __launch_bounds__(1024) void k_glf(GeoK G, double gamma, const double
     double m0 = 0.0, m1 = 0.0, m2 = 0.0;
     for (long t = (long)bb * blockDim.x + threadIdx.x; t < total; t += (long)bpd * blockDim.x) {
         long r;
-        int sg;
+        int seg;
         if (d == 0) {
-            sg = (int)(t % nseg);
+            seg = (int)(t % nseg);
             r = t / nseg;
         } else {
             r = t % n12;
-            sg = (int)(t / n12);
+            seg = (int)(t / n12);
         }
-        const int f0 = sg * kGlfSeg - 1;
+        const int f0 = seg * kGlfSeg - 1;
         const long line = G.base + (r % n1) * G.sd[e1] + (r / n1) * G.sd[e2];
         double u[NW][DIM], cs[NW];
 #pragma unroll
@@ -980,7 +1178,7 @@ __global__ __launch_bounds__(1024) void k_glf(GeoK G, double gamma, const double
             // nodes past the last face's stencil are never read: clamp them
             int p = min(f0 - LO + j, nd + LO);
             if (per) p = p < 0 ? p + nd : (p >= nd ? p - nd : p);
-            glf_node<DIM>(q, G.vol, line + (long)p * sdd, gamma, u[j], cs[j]);
+            glf_node<DIM>(q, G.vol, line + (long)p * sdd, gm1, sg, u[j], cs[j]);
         }
 #pragma unroll
         for (int j = 0; j < kGlfSeg; ++j) {
@@ -1000,11 +1198,11 @@ __global__ __launch_bounds__(1024) void k_glf(GeoK G, double gamma, const double
             double s2 = 0.0;
 #pragma unroll
             for (int c = 0; c < DIM; ++c) s2 += sf[c] * sf[c];
-            const double sn = sqrt(s2);
-            const double sigma = sn / Vf;
+            const double isn = drsq1(s2);  // as in the face's basis (roe)
+            const double sigma = s2 * isn * drcp1(Vf);
             double n[DIM];
 #pragma unroll
-            for (int c = 0; c < DIM; ++c) n[c] = sf[c] / sn;
+            for (int c = 0; c < DIM; ++c) n[c] = sf[c] * isn;
 #pragma unroll
             for (int m = 0; m <= 2 * LO + 1; ++m) {
                 double un = 0.0;
@@ -1276,6 +1474,8 @@ struct SweepArgs {
     int nseg[3];
     int glf;  // 1: reduce the global LF speeds of the stage input into sk.glf first
     double* glf_next;  // the speed set the reduction zeroes for the next stage (or NULL)
+    double* glf_time;  // the device time the reduction advances by time_dt (or NULL)
+    double time_dt;
     Probe* probe;      // instrumented step (or NULL)
 };
 

@@ -476,9 +476,6 @@ __global__ __launch_bounds__(256) void k_bc_face(GeoK G, BcK bc, const double* _
     }
 }
 
-// The time of a captured step sequence, T = {t, t0, steps}: set before the
-// replays; at the end of every step steps += 1 and t = t0 + steps dt (the
-// step start times of an uncaptured run, without accumulated rounding).
 __global__ void k_time_set(double* T, double t0) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         T[0] = t0;
@@ -487,11 +484,7 @@ __global__ void k_time_set(double* T, double t0) {
     }
 }
 __global__ void k_time_advance(double* T, double dt) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        const double n = T[2] + 1.0;
-        T[2] = n;
-        T[0] = T[1] + n * dt;
-    }
+    if (threadIdx.x == 0 && blockIdx.x == 0) time_advance(T, dt);
 }
 
 // ---------------------------------------------------------------------------
