@@ -529,7 +529,7 @@ template <int DIM>
 __device__ __forceinline__ void visc_prim(const double* __restrict__ q, long vol, long o, double gm1,
                                           double (&w)[DIM + 1]) {
     const double rho = q[o];
-    const double ir = 1.0 / rho;
+    const double ir = drcp(rho);
     double k2 = 0.0;
 #pragma unroll
     for (int c = 0; c < DIM; ++c) {
@@ -547,14 +547,14 @@ __device__ __forceinline__ void visc_prim(const double* __restrict__ q, long vol
 // du_j/dx_i - 2/3 delta_ij div u), the physical fluxes (tau_1j .. tau_nj,
 // u_i tau_ij + kappa dT/dx_j) and Fv~_d = sum_j s_{d,j} Fv_j.  fv: [DIM
 // directions][DIM + 1 components] arrays in the state layout (the mass
-// component, zero, is not stored).
+// component, zero, is not stored).  m: the node's metrics, 1/J last.
 template <int DIM>
 __device__ __forceinline__ void visc_node_fluxes(const GeoK& G, double mu, double kappa,
-                                                 const double* __restrict__ met, long o,
+                                                 const double (&m)[DIM * DIM + 1], long o,
                                                  const double (&dphi)[DIM][DIM + 1], const double (&w)[DIM + 1],
                                                  double* __restrict__ fv) {
-    constexpr int NP = DIM + 1, NMET = DIM == 3 ? 10 : 5;
-    const double iV = 1.0 / met[(NMET - 1) * G.vol + o];
+    constexpr int NP = DIM + 1;
+    const double iV = drcp(m[DIM * DIM]);
     double grad[NP][DIM];
 #pragma unroll
     for (int a = 0; a < NP; ++a)
@@ -564,7 +564,7 @@ __device__ __forceinline__ void visc_node_fluxes(const GeoK& G, double mu, doubl
     for (int d = 0; d < DIM; ++d)
 #pragma unroll
         for (int j = 0; j < DIM; ++j) {
-            const double sdj = met[(d * DIM + j) * G.vol + o] * iV;
+            const double sdj = m[d * DIM + j] * iV;
 #pragma unroll
             for (int a = 0; a < NP; ++a) grad[a][j] += sdj * dphi[d][a];
         }
@@ -589,7 +589,7 @@ __device__ __forceinline__ void visc_node_fluxes(const GeoK& G, double mu, doubl
         for (int v = 0; v < NP; ++v) {
             double sum = 0.0;
 #pragma unroll
-            for (int j = 0; j < DIM; ++j) sum += met[(d * DIM + j) * G.vol + o] * F[j][v];
+            for (int j = 0; j < DIM; ++j) sum += m[d * DIM + j] * F[j][v];
             fv[(d * NP + v) * G.vol + o] = sum;
         }
 }
@@ -621,7 +621,10 @@ __global__ __launch_bounds__(256) void k_visc_flux(GeoK G, double gamma, double 
     }
     double w[NP];
     visc_prim<DIM>(q, G.vol, o, gm1, w);
-    visc_node_fluxes<DIM>(G, mu, kappa, met, o, dphi, w, fv);
+    double m[DIM * DIM + 1];
+#pragma unroll
+    for (int c = 0; c <= DIM * DIM; ++c) m[c] = met[c * G.vol + o];
+    visc_node_fluxes<DIM>(G, mu, kappa, m, o, dphi, w, fv);
 }
 
 // R = sum_d D6_d(Fv~_d) at every interior node of a 2D block (the mass
@@ -651,13 +654,23 @@ __global__ __launch_bounds__(256) void k_visc_div(GeoK G, const double* __restri
 }
 
 // 3D blocks: a workgroup (one lane per column) owns a kVmI (i) x kVmJ (j)
-// tile of columns and a run of kVmK planes, and marches along k.  Each lane keeps the seven planes
-// k-3 .. k+3 of its own column in registers (the zeta differences) and per
-// plane the tile with a halo of three nodes in i and j is staged in LDS (the
-// xi and eta differences): per node about 15 loads of q instead of 95, and
-// every plane is read once per tile.  All axes are periodic, so every index
-// wraps; lanes past the grid's edge load wrapped nodes and store nothing.
-constexpr int kVmI = 64, kVmJ = 8, kVmK = 32, kVmHI = kVmI + 6, kVmHJ = kVmJ + 6;
+// tile of columns and a run of planes, and marches along k.  Each lane keeps
+// the seven planes k-3 .. k+3 of its own column in registers (the zeta
+// differences) and per plane the tile with a halo of three nodes in i and j
+// is staged in LDS (the xi and eta differences): the tile from the lanes'
+// registers, the halo by one load per lane at most.  Everything a plane needs
+// from memory is asked for a plane ahead, and the LDS plane is double
+// buffered, so that one barrier a plane is all that waits.  All axes are
+// periodic, so every index wraps; lanes past the grid's edge load wrapped
+// nodes and store nothing.
+// Bound by HBM: 352 algorithmic bytes per node.  The tile is 32 x 16: half
+// the halo of 64 x 8 and, with 160 nodes, no idle lanes.  Runs of 16 planes
+// (six more fill the registers) give a 160^3 block 800 workgroups; 32 planes
+// left a workgroup per CU.  160^3: fluxes 227 us, divergence 157 (3.9 and
+// 3.6 TB/s),
+// against 329 and 200 with the halo and the tile loaded again from memory,
+// two barriers a plane, and no load ahead.
+constexpr int kVmI = 32, kVmJ = 16, kVmK = 16, kVmHI = kVmI + 6, kVmHJ = kVmJ + 6, kVmT = kVmI * kVmJ;
 inline long visc_march_blocks(const int n[3]) {
     return (long)((n[0] + kVmI - 1) / kVmI) * ((n[1] + kVmJ - 1) / kVmJ) * ((n[2] + kVmK - 1) / kVmK);
 }
@@ -681,33 +694,90 @@ __device__ __forceinline__ VmTile vm_tile(const GeoK& G) {
     t.j = j % G.n[1];
     return t;
 }
-__device__ __forceinline__ long vm_off(const GeoK& G, int i, int j, int k) {
-    return G.base + i + (long)j * G.sd[1] + (long)k * G.sd[2];
+// the halo entry e (0 .. kVmHalo - 1) of the tile: columns left and right of
+// it, then rows below and above (with the corners, which the fluxes' and the
+// divergence's differences do not read, left out): entry (hi, hj) of the
+// kVmHI x kVmHJ box
+constexpr int kVmHalo = 6 * kVmJ + 6 * kVmI;
+static_assert(kVmHalo <= kVmT, "one halo entry per lane");
+__device__ __forceinline__ void vm_halo(int e, int& hi, int& hj) {
+    if (e < 6 * kVmJ) {
+        hi = e % 6;
+        hj = 3 + e / 6;
+        if (hi >= 3) hi += kVmI;
+    } else {
+        e -= 6 * kVmJ;
+        hi = 3 + e % kVmI;
+        hj = e / kVmI;
+        if (hj >= 3) hj += kVmJ;
+    }
+}
+// element offset of node (i, j, k)
+__device__ __forceinline__ unsigned vm_off(const GeoK& G, int i, int j, int k) {
+    return (unsigned)(G.base + i + (long)j * G.sd[1] + (long)k * G.sd[2]);
 }
 
-__global__ __launch_bounds__(kVmI * kVmJ) void k_visc_flux3(GeoK G, double gamma, double mu, double kappa,
+__global__ __launch_bounds__(kVmT) void k_visc_flux3(GeoK G, double gamma, double mu, double kappa,
                                                      const double* __restrict__ met,
                                                      const double* __restrict__ q, double* __restrict__ fv) {
-    __shared__ double L[4][kVmHJ][kVmHI];  // primitives of plane k, tile and halo
+    __shared__ double L[2][4][kVmHJ][kVmHI];  // primitives of plane k, tile and halo
     const VmTile t = vm_tile(G);
     const double gm1 = gamma - 1.0;
     const int li = (int)(threadIdx.x % kVmI) + 3, lj = (int)(threadIdx.x / kVmI) + 3;
-    double P[7][4];  // this column's primitives at planes k-3 .. k+3
+    const bool halo = (int)threadIdx.x < kVmHalo;
+    int hi = 0, hj = 0;
+    if (halo) vm_halo((int)threadIdx.x, hi, hj);
+    const unsigned col = vm_off(G, t.i, t.j, 0);
+    const unsigned hcol =
+        vm_off(G, (t.i0 - 3 + hi + 2 * G.n[0]) % G.n[0], (t.j0 - 3 + hj + 2 * G.n[1]) % G.n[1], 0);
+    const unsigned sk = (unsigned)G.sd[2];
+    auto load = [&](unsigned o, double (&v)[5]) {
 #pragma unroll
-    for (int r = 0; r < 6; ++r) visc_prim<3>(q, G.vol, vm_off(G, t.i, t.j, wrapi(t.k0 - 3 + r, G.n[2])), gm1, P[r]);
-    for (int k = t.k0; k < t.k1; ++k) {
-        visc_prim<3>(q, G.vol, vm_off(G, t.i, t.j, wrapi(k + 3, G.n[2])), gm1, P[6]);
-        __syncthreads();  // the previous plane's reads are done
-        for (int e = threadIdx.x; e < kVmHI * kVmHJ; e += blockDim.x) {
-            const int hi = e % kVmHI, hj = e / kVmHI;
-            double w[4];
-            visc_prim<3>(q, G.vol,
-                         vm_off(G, (t.i0 - 3 + hi + 2 * G.n[0]) % G.n[0], (t.j0 - 3 + hj + 2 * G.n[1]) % G.n[1], k),
-                         gm1, w);
+        for (int c = 0; c < 5; ++c) v[c] = q[c * G.vol + o];
+    };
+    // (u, T) of a node from its conserved state
+    auto prim = [&](const double (&v)[5], double (&w)[4]) {
+        const double ir = drcp(v[0]);
+        double k2 = 0.0;
 #pragma unroll
-            for (int a = 0; a < 4; ++a) L[a][hj][hi] = w[a];
+        for (int c = 0; c < 3; ++c) {
+            w[c] = v[1 + c] * ir;
+            k2 += v[1 + c] * w[c];
         }
-        __syncthreads();
+        w[3] = gm1 * (v[4] - 0.5 * k2) * ir;
+    };
+    double P[7][4];  // this column's primitives at planes k-3 .. k+3
+    double qc[5], qh[5];
+#pragma unroll
+    for (int r = 0; r < 6; ++r) {
+        load(col + (unsigned)wrapi(t.k0 - 3 + r, G.n[2]) * sk, qc);
+        prim(qc, P[r]);
+    }
+    load(col + (unsigned)wrapi(t.k0 + 3, G.n[2]) * sk, qc);
+    if (halo) load(hcol + (unsigned)t.k0 * sk, qh);
+    for (int k = t.k0; k < t.k1; ++k) {
+        double(*Lk)[kVmHJ][kVmHI] = L[(k - t.k0) & 1];
+        prim(qc, P[6]);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) Lk[a][lj][li] = P[3][a];
+        if (halo) {
+            double w[4];
+            prim(qh, w);
+#pragma unroll
+            for (int a = 0; a < 4; ++a) Lk[a][hj][hi] = w[a];
+        }
+        if (k + 1 < t.k1) {
+            load(col + (unsigned)wrapi(k + 4, G.n[2]) * sk, qc);
+            if (halo) load(hcol + (unsigned)(k + 1) * sk, qh);
+        }
+        const unsigned o = col + (unsigned)k * sk;
+        double m[10];
+#pragma unroll
+        for (int c = 0; c < 10; ++c) m[c] = met[c * G.vol + o];
+        // one barrier a plane: a lane overwrites this buffer two planes on,
+        // past the next plane's barrier, which every lane reaches only after
+        // its reads of this plane
+        lds_barrier();
         double dphi[3][4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
@@ -716,12 +786,12 @@ __global__ __launch_bounds__(kVmI * kVmJ) void k_visc_flux3(GeoK G, double gamma
             dphi[2][a] = 0.0;
 #pragma unroll
             for (int s = 1; s <= 3; ++s) {
-                dphi[0][a] += d6w(s) * (L[a][lj][li + s] - L[a][lj][li - s]);
-                dphi[1][a] += d6w(s) * (L[a][lj + s][li] - L[a][lj - s][li]);
+                dphi[0][a] += d6w(s) * (Lk[a][lj][li + s] - Lk[a][lj][li - s]);
+                dphi[1][a] += d6w(s) * (Lk[a][lj + s][li] - Lk[a][lj - s][li]);
                 dphi[2][a] += d6w(s) * (P[3 + s][a] - P[3 - s][a]);
             }
         }
-        if (t.mine) visc_node_fluxes<3>(G, mu, kappa, met, vm_off(G, t.i, t.j, k), dphi, P[3], fv);
+        if (t.mine) visc_node_fluxes<3>(G, mu, kappa, m, o, dphi, P[3], fv);
 #pragma unroll
         for (int r = 0; r < 6; ++r)
 #pragma unroll
@@ -729,51 +799,67 @@ __global__ __launch_bounds__(kVmI * kVmJ) void k_visc_flux3(GeoK G, double gamma
     }
 }
 
-__global__ __launch_bounds__(kVmI * kVmJ) void k_visc_div3(GeoK G, const double* __restrict__ fv, double* __restrict__ R) {
-    __shared__ double Lx[4][kVmJ][kVmHI];  // Fv~_xi of plane k: tile rows, halo in i
-    __shared__ double Ly[4][kVmHJ][kVmI];  // Fv~_eta of plane k: tile columns, halo in j
+__global__ __launch_bounds__(kVmT) void k_visc_div3(GeoK G, const double* __restrict__ fv, double* __restrict__ R) {
+    __shared__ double Lx[2][4][kVmJ][kVmHI];  // Fv~_xi of plane k: tile rows, halo in i
+    __shared__ double Ly[2][4][kVmHJ][kVmI];  // Fv~_eta of plane k: tile columns, halo in j
     const VmTile t = vm_tile(G);
     const int ti = (int)(threadIdx.x % kVmI), tj = (int)(threadIdx.x / kVmI);
+    const bool halo = (int)threadIdx.x < kVmHalo;
+    int hi = 0, hj = 0;
+    if (halo) vm_halo((int)threadIdx.x, hi, hj);
+    const bool hx = (int)threadIdx.x < 6 * kVmJ;  // the halo entry is one of Lx
+    const unsigned col = vm_off(G, t.i, t.j, 0);
+    const unsigned hcol =
+        vm_off(G, (t.i0 - 3 + hi + 2 * G.n[0]) % G.n[0], (t.j0 - 3 + hj + 2 * G.n[1]) % G.n[1], 0);
+    const unsigned sk = (unsigned)G.sd[2];
+    auto load = [&](int d, unsigned o, double (&v)[4]) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = fv[(4 * d + c) * G.vol + o];
+    };
     double Z[7][4];  // this column's Fv~_zeta at planes k-3 .. k+3
+    double X[4], Yv[4], H[4], Zn[4];
 #pragma unroll
-    for (int r = 0; r < 6; ++r) {
-        const long off = vm_off(G, t.i, t.j, wrapi(t.k0 - 3 + r, G.n[2]));
-#pragma unroll
-        for (int v = 0; v < 4; ++v) Z[r][v] = fv[(8 + v) * G.vol + off];
-    }
+    for (int r = 0; r < 6; ++r) load(2, col + (unsigned)wrapi(t.k0 - 3 + r, G.n[2]) * sk, Z[r]);
+    auto ahead = [&](int k) {
+        load(2, col + (unsigned)wrapi(k + 3, G.n[2]) * sk, Zn);
+        load(0, col + (unsigned)k * sk, X);
+        load(1, col + (unsigned)k * sk, Yv);
+        if (halo) load(hx ? 0 : 1, hcol + (unsigned)k * sk, H);
+    };
+    ahead(t.k0);
     for (int k = t.k0; k < t.k1; ++k) {
-        {
-            const long off = vm_off(G, t.i, t.j, wrapi(k + 3, G.n[2]));
+        double(*Xk)[kVmJ][kVmHI] = Lx[(k - t.k0) & 1];
+        double(*Yk)[kVmHJ][kVmI] = Ly[(k - t.k0) & 1];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) Z[6][v] = fv[(8 + v) * G.vol + off];
+        for (int v = 0; v < 4; ++v) {
+            Z[6][v] = Zn[v];
+            Xk[v][tj][ti + 3] = X[v];
+            Yk[v][tj + 3][ti] = Yv[v];
         }
-        __syncthreads();
-        for (int e = threadIdx.x; e < kVmHI * kVmJ; e += blockDim.x) {
-            const int hi = e % kVmHI, hj = e / kVmHI;
-            const long off = vm_off(G, (t.i0 - 3 + hi + 2 * G.n[0]) % G.n[0], (t.j0 + hj) % G.n[1], k);
+        if (halo) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) Lx[v][hj][hi] = fv[v * G.vol + off];
+            for (int v = 0; v < 4; ++v) {
+                if (hx)
+                    Xk[v][hj - 3][hi] = H[v];
+                else
+                    Yk[v][hj][hi - 3] = H[v];
+            }
         }
-        for (int e = threadIdx.x; e < kVmI * kVmHJ; e += blockDim.x) {
-            const int hi = e % kVmI, hj = e / kVmI;
-            const long off = vm_off(G, (t.i0 + hi) % G.n[0], (t.j0 - 3 + hj + 2 * G.n[1]) % G.n[1], k);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) Ly[v][hj][hi] = fv[(4 + v) * G.vol + off];
-        }
-        __syncthreads();
+        if (k + 1 < t.k1) ahead(k + 1);
+        lds_barrier();
         double acc[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             acc[v] = 0.0;
 #pragma unroll
-            for (int s = 1; s <= 3; ++s) acc[v] += d6w(s) * (Lx[v][tj][ti + 3 + s] - Lx[v][tj][ti + 3 - s]);
+            for (int s = 1; s <= 3; ++s) acc[v] += d6w(s) * (Xk[v][tj][ti + 3 + s] - Xk[v][tj][ti + 3 - s]);
 #pragma unroll
-            for (int s = 1; s <= 3; ++s) acc[v] += d6w(s) * (Ly[v][tj + 3 + s][ti] - Ly[v][tj + 3 - s][ti]);
+            for (int s = 1; s <= 3; ++s) acc[v] += d6w(s) * (Yk[v][tj + 3 + s][ti] - Yk[v][tj + 3 - s][ti]);
 #pragma unroll
             for (int s = 1; s <= 3; ++s) acc[v] += d6w(s) * (Z[3 + s][v] - Z[3 - s][v]);
         }
         if (t.mine) {
-            const long o = vm_off(G, t.i, t.j, k);
+            const unsigned o = col + (unsigned)k * sk;
             R[o] = 0.0;
 #pragma unroll
             for (int v = 0; v < 4; ++v) R[(1 + v) * G.vol + o] = acc[v];
