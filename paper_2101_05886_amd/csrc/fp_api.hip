@@ -186,41 +186,71 @@ SchemeK make_sk(const fp_scheme* s) {
     return k;
 }
 
-// Segment length (nodes per item) of a sweep along an axis of nd nodes with
-// `lblocks` blocks of 64 lines: an item of S nodes evaluates its S + 1 faces
-// four at a time.  The plan minimises (rounds of resident workgroups, two on
-// each of 256 CUs) x (iterations + 1/2 per workgroup): filling the ring costs
-// an item about half an iteration.  S = 3, one iteration, is the shortest,
-// and the best for blocks too small to fill the chip (a 45x33x29 residual:
-// 30.2 us with S = 4, two iterations, 24.0 with 3).
-int plan_segment(int nd, long lblocks) {
+// The split of an eta / zeta sweep along an axis of nd nodes with `lblocks`
+// blocks of 64 lines over the resident workgroups (two on each of 256 CUs).
+// A workgroup evaluates the S + 1 faces of S nodes four at a time; filling its
+// ring costs it about half an iteration more.  In half iterations:
+//   uniform segments cost (rounds of resident workgroups) x (2 iterations + 1)
+//     and leave part of the chip idle in the last round (160^3: 400 line
+//     blocks, one round of whole lines with 112 of 512 places empty, or four
+//     of 32 nodes);
+//   balanced quotas give every workgroup the same nodes in one round, but
+//     those that cross a line block's end pay for a second piece.
+// The cheaper one is taken, balanced quotas only from 16 nodes per workgroup
+// (below, launches last as long as one chain of load, face and store) to
+// `longest`: workgroups that march far drift apart and lose the cache lines
+// they share with their neighbours, which LU5, nearest to the HBM bound,
+// feels first.  RK3 step, uniform and balanced: 145x113x97 WENO5 FP64 937
+// and 904 us, 160^3 2,328 and 2,276, 180x120x150 LU5 1,190 and 1,165; above
+// the limit 200^3 LU5 2,835 and 3,112, WENO5 mixed 3,855 and 3,903.  S = 3, one iteration, is the shortest segment, and
+// the best for blocks too small to fill the chip (a 45x33x29 residual: 30.2
+// us with S = 4, two iterations, 24.0 with 3).
+long piece_cost(long nodes) { return 2 * ((nodes + 4) / 4) + 1; }
+
+WgSplit plan_split(int nd, long lblocks, long longest) {
     const long resident = 512;
+    WgSplit w{nd, false, 0};
     long best = -1;
-    int bestS = nd;
     for (int ns = 1; ns <= nd; ++ns) {
         const int S = (nd + ns - 1) / ns;
         if (S < 3 && ns > 1) break;
         const long segs = (nd + S - 1) / S;
-        const long iters = (S + 4) / 4;
-        const long rounds = (lblocks * segs + resident - 1) / resident;
-        const long cost = rounds * (2 * iters + 1);
+        const long cost = (lblocks * segs + resident - 1) / resident * piece_cost(S);
         if (best < 0 || cost < best) {
             best = cost;
-            bestS = S;
+            w.S = S;
+            w.wgs = (unsigned)(lblocks * segs);
         }
     }
-    return bestS;
+    const long total = lblocks * nd;
+    if (total < 16 * resident) return w;
+    const long quota = (total + resident - 1) / resident | 3;  // 4 m - 1 nodes: m full iterations
+    if (quota > longest) return w;
+    const long wgs = (total + quota - 1) / quota;
+    long worst = 0;
+    for (long g = 0; g < wgs && worst < best; ++g) {
+        long k = g * quota % nd, left = std::min(quota, total - g * quota), cost = 0;
+        for (; left > 0; k = 0) {
+            const long m = std::min(left, nd - k);
+            cost += piece_cost(m);
+            left -= m;
+        }
+        worst = std::max(worst, cost);
+    }
+    if (worst < best) {
+        w.S = (int)quota;
+        w.balanced = true;
+        w.wgs = (unsigned)wgs;
+    }
+    return w;
 }
 
-void plan_segments(const GeoK& G, int ndim, SweepArgs& a) {
-    for (int d = 1; d < ndim; ++d) {
+// the splits of the sweeps of a block
+void plan_sweeps(const GeoK& G, const fp_grid& g, const fp_scheme& sch, SweepArgs& a) {
+    for (int d = 1; d < g.ndim; ++d) {
         const int oth = d == 1 ? 2 : 1;
-        const long lblocks = ((long)G.n[0] * G.n[oth] + 63) / 64;
-        a.S[d] = plan_segment(G.n[d], lblocks);
-        a.nseg[d] = (G.n[d] + a.S[d] - 1) / a.S[d];
+        a.split[d] = plan_split(G.n[d], ((long)G.n[0] * G.n[oth] + 63) / 64, sch.recon == FP_LINUP5 ? 111 : 127);
     }
-    a.S[0] = a.nseg[0] = 0;
-    if (ndim == 2) a.S[2] = a.nseg[2] = 0;
 }
 
 struct Ctx {
@@ -299,7 +329,7 @@ hipError_t run_residual(const Ctx& c, const double* met, const double* qs, doubl
     a.ep_first = epi(visc ? EPI_MID : EPI_FIRST, R);
     a.ep_mid = epi(EPI_MID, R);
     a.ep_last = last;
-    plan_segments(c.G, c.grid.ndim, a);
+    plan_sweeps(c.G, c.grid, c.sch, a);
     return c.stage(a, s);
 }
 
@@ -379,6 +409,9 @@ hipError_t run_rk3(const Ctx& c, const double* met, double* q, double* work, dou
     double* out[3] = {A, B, q};
     const double ca[3] = {0.0, 3.0 / 4.0, 1.0 / 3.0};
     const double cb[3] = {1.0, 1.0 / 4.0, 2.0 / 3.0};
+    SweepArgs plan;  // the same for every stage
+    std::memset(&plan, 0, sizeof plan);
+    plan_sweeps(c.G, c.grid, c.sch, plan);
     for (int k = 0; k < 3; ++k) {
         if (bc) launch_bcs(c, *bc, met, const_cast<double*>(in[k]), stage_t[k], s, tdev, probe);
         if (visc) launch_viscous(c, met, in[k], vwork, R, s, probe);
@@ -409,7 +442,7 @@ hipError_t run_rk3(const Ctx& c, const double* met, double* q, double* work, dou
         a.ep_first = epi(visc ? EPI_MID : EPI_FIRST, R);
         a.ep_mid = epi(EPI_MID, R);
         a.ep_last = e;
-        plan_segments(c.G, c.grid.ndim, a);
+        std::memcpy(a.split, plan.split, sizeof a.split);
         hipError_t err = c.stage(a, s);
         if (err != hipSuccess) return err;
     }
@@ -884,7 +917,7 @@ fp_status fp_residual_dir(const fp_grid* g, const fp_scheme* sch, const double* 
     a.sk = c.sk;
     a.met = met;
     a.qs = q;
-    plan_segments(c.G, g->ndim, a);
+    plan_sweeps(c.G, *g, *sch, a);
     hipError_t e = f(a, dir, epi(accumulate ? EPI_MID : EPI_FIRST, acc), (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "fp_residual_dir launch");
     return FP_OK;
@@ -1208,7 +1241,9 @@ fp_status fp_max_dt(const fp_grid* g, const fp_scheme* sch, const double* met, c
     const long tot = (long)G.n[0] * G.n[1] * G.n[2];
     unsigned long long* bits = reinterpret_cast<unsigned long long*>(dt_dev);
     hipLaunchKernelGGL(k_dt_init, dim3(1), dim3(1), 0, s, bits);
-    const unsigned blocks = (unsigned)((tot + 255) / 256);
+    // (each block folds its maximum in by an atomic, and those serialise:
+    // about 11 ns each)
+    const unsigned blocks = (unsigned)std::min((tot + 255) / 256, 2048L);
     if (g->ndim == 3)
         hipLaunchKernelGGL(k_dt_reduce<3>, dim3(blocks), dim3(256), 0, s, G, sch->gamma, met, q, bits);
     else

@@ -32,10 +32,13 @@ inline SchemeK dir_sk(const SchemeK& sk, int d) {
 
 template <int DIM, int DIR, int Y, int MODE>
 void launch_wg_mode(const SweepArgs& a, const EpiK& ep, hipStream_t s) {
-    constexpr int OTH = DIR == 1 ? 2 : 1;
-    const long lblocks = ((long)a.G.n[0] * a.G.n[OTH] + 63) / 64;
-    hipLaunchKernelGGL((k_sweep_wg<DIM, DIR, R, Y, P, MODE>), dim3((unsigned)(lblocks * a.nseg[DIR])),
-                       dim3(256), 0, s, a.G, dir_sk(a.sk, DIR), a.met, a.qs, ep, a.S[DIR]);
+    const WgSplit& w = a.split[DIR];
+    if (w.balanced)
+        hipLaunchKernelGGL((k_sweep_wg<DIM, DIR, R, Y, P, MODE, true>), dim3(w.wgs), dim3(256), 0, s, a.G,
+                           dir_sk(a.sk, DIR), a.met, a.qs, ep, w.S);
+    else
+        hipLaunchKernelGGL((k_sweep_wg<DIM, DIR, R, Y, P, MODE, false>), dim3(w.wgs), dim3(256), 0, s, a.G,
+                           dir_sk(a.sk, DIR), a.met, a.qs, ep, w.S);
 }
 
 template <int DIM, int DIR, int Y>

@@ -743,10 +743,9 @@ __device__ __forceinline__ void wg_convert(WgLds<DIM, WIDE>& L, int slot, double
     }
 }
 
-// eta / zeta sweeps: a workgroup of four waves owns 64 grid lines along DIR
-// (consecutive in the flattened (i, other) index, so row loads are
-// coalesced) and one segment [k0, k1) of S nodes of them; work item `item`
-// of a block is (line block = item % lblocks, segment = item / lblocks).
+// eta / zeta sweeps: a workgroup of four waves takes a block of 64 grid lines
+// along DIR (consecutive in the flattened (i, other) index, so row loads are
+// coalesced) and one segment [k0, k1) of their nodes.
 // The stencil rows are staged in an LDS ring by global-to-LDS DMA, one row
 // per wave per iteration, prefetched one iteration ahead.  Per iteration
 // wave w evaluates the face f+1/2, f = k0 - 1 + 4 it + w, on its 64 lines
@@ -762,7 +761,7 @@ __device__ __forceinline__ void wg_convert(WgLds<DIM, WIDE>& L, int slot, double
 template <int DIM, int DIR, int RECON, int Y, int PREC>
 __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
                                               const double* __restrict__ met, const double* qs,
-                                              const EpiK& ep, int S, long item,
+                                              const EpiK& ep, int lineblk, int k0, int k1,
                                               WgLds<DIM, wide_stencil(RECON, Y)>& L) {
     using W = WgLds<DIM, wide_stencil(RECON, Y)>;
     constexpr int NV = DIM + 2;
@@ -771,10 +770,7 @@ __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
     const int lane = threadIdx.x & 63;
     const int w = wave_id();
     const long nlines = (long)G.n[0] * G.n[OTH];
-    const long lblocks = (nlines + 63) / 64;
-    const long lineblk = item % lblocks;
-    const int seg = (int)(item / lblocks);
-    const long line = lineblk * 64 + lane;
+    const long line = lineblk * 64L + lane;
     const bool lane_ok = line < nlines;
     const int i = lane_ok ? (int)(line % G.n[0]) : 0;
     const int o = lane_ok ? (int)(line / G.n[0]) : 0;
@@ -784,7 +780,7 @@ __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
     unsigned loff[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        long ln = lineblk * 64 + 32 * h + (lane >> 1);
+        long ln = lineblk * 64L + 32 * h + (lane >> 1);
         ln = ln < nlines ? ln : nlines - 1;
         const long off = G.base + ln % G.n[0] + (ln / G.n[0]) * G.sd[OTH];
         loff[h] = (unsigned)off * 8u + (unsigned)(lane & 1) * 4u;
@@ -793,8 +789,6 @@ __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
     const int per = G.bc[DIR] == 0;
     const int sdD = (int)G.sd[DIR];
     const long vol = G.vol;
-    const int k0 = seg * S;
-    const int k1 = min(k0 + S, nd);
     const int iters = (k1 - k0 + 1 + 3) / 4;  // faces k0-1/2 .. k1-1/2
     const int tb = k0 - 1 - W::LO;            // node index of ring row 0
     const int tmax = k1 - 1 + W::HI;          // last row any needed face reads
@@ -886,17 +880,46 @@ inline long sweep_wg_items(const int n[3], int dir, int S) {
     return lblocks * ((n[dir] + S - 1) / S);
 }
 
+// How the eta / zeta sweep of one block is split over `wgs` workgroups.
+// Uniform: workgroup b takes segment b / lblocks, of S nodes, of line block
+// b % lblocks.  Balanced: the nodes of all line blocks are numbered one block
+// after another and each workgroup takes S of them, as one piece or, across
+// the end of a line block, more.
+struct WgSplit {
+    int S;
+    bool balanced;
+    unsigned wgs;
+};
+
 // One launch of the eta / zeta sweep of one block, with its epilogue mode
 // (EPI_*) fixed at compile time, as in the batched sweeps, so that only that
 // epilogue's registers are allocated.
-template <int DIM, int DIR, int RECON, int Y, int PREC, int MODE>
+// (the loop over pieces costs registers, so the splits are kernels apart)
+template <int DIM, int DIR, int RECON, int Y, int PREC, int MODE, bool BALANCED>
 __global__ __launch_bounds__(256) FP_SWEEP_ATTR void k_sweep_wg(GeoK G, SchemeK sk,
                                                                 const double* __restrict__ met,
                                                                 const double* qs, EpiK ep, int S) {
     __shared__ WgLds<DIM, wide_stencil(RECON, Y)> lds;
+    constexpr int OTH = DIR == 1 ? 2 : 1;
     EpiK e = ep;
     e.mode = MODE;
-    sweep_wg_item<DIM, DIR, RECON, Y, PREC>(G, sk, met, qs, e, S, blockIdx.x, lds);
+    const unsigned lblocks = (unsigned)(((long)G.n[0] * G.n[OTH] + 63) / 64);
+    const int nd = G.n[DIR];
+    if constexpr (!BALANCED) {
+        const int k0 = (int)(blockIdx.x / lblocks) * S;
+        sweep_wg_item<DIM, DIR, RECON, Y, PREC>(G, sk, met, qs, e, (int)(blockIdx.x % lblocks), k0, min(k0 + S, nd),
+                                                lds);
+    } else {
+        const unsigned u = blockIdx.x * (unsigned)S;
+        unsigned lineblk = u / (unsigned)nd;
+        int k0 = (int)(u - lineblk * (unsigned)nd);
+        for (int left = S; left > 0 && lineblk < lblocks; ++lineblk, k0 = 0) {
+            const int k1 = min(nd, k0 + left);
+            sweep_wg_item<DIM, DIR, RECON, Y, PREC>(G, sk, met, qs, e, (int)lineblk, k0, k1, lds);
+            left -= k1 - k0;
+            __syncthreads();  // the next piece rewrites the LDS ring
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1403,8 +1426,12 @@ __global__ __launch_bounds__(256) FP_SWEEP_ATTR void kb_sweep_wg(const int* __re
         b = advance_block(st, nblk, b, item);
         const BBlock& B = t_blk[ord[b]];
         const EpiK ep = stage_epi(B, stage, MODE, DIM);
-        sweep_wg_item<DIM, DIR, RECON, Y, PREC>(B.G, sk, B.met, stage_in(B, stage), ep, B.S[DIR],
-                                                item - st[b], lds);
+        constexpr int OTH = DIR == 1 ? 2 : 1;
+        const unsigned lblocks = (unsigned)(((long)B.G.n[0] * B.G.n[OTH] + 63) / 64);
+        const unsigned in = (unsigned)(item - st[b]);
+        const int k0 = (int)(in / lblocks) * B.S[DIR];
+        sweep_wg_item<DIM, DIR, RECON, Y, PREC>(B.G, sk, B.met, stage_in(B, stage), ep, (int)(in % lblocks), k0,
+                                                min(k0 + B.S[DIR], B.G.n[DIR]), lds);
         __syncthreads();  // the next item rewrites the LDS ring
     }
 }
@@ -1470,8 +1497,7 @@ struct SweepArgs {
     const double* met;
     const double* qs;
     EpiK ep_first, ep_mid, ep_last;
-    int S[3];
-    int nseg[3];
+    WgSplit split[3];
     int glf;  // 1: reduce the global LF speeds of the stage input into sk.glf first
     double* glf_next;  // the speed set the reduction zeroes for the next stage (or NULL)
     double* glf_time;  // the device time the reduction advances by time_dt (or NULL)
