@@ -356,7 +356,10 @@ fp_status fp_batch_rk3_step(fp_batch *batch, void *stream);
  * frozen ghost layers of each block's q are copied into its stage registers
  * once, at the start of the call (no step writes them; so ghost values the
  * caller changes take effect at the next call), then the graph, which holds
- * the stages only, runs nsteps times. */
+ * the stages only, runs nsteps times.
+ * The 2D blocks of a batch that also holds 3D ones advance on a stream of
+ * the batch's own, ordered after the work `stream` holds at the call and
+ * before what it is given afterwards. */
 fp_status fp_batch_solve(fp_batch *batch, int64_t nsteps, void *stream);
 
 /* Multi-block interfaces.  A link makes the ghost layers of `block` on
