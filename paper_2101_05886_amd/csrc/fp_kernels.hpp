@@ -274,6 +274,20 @@ struct StagedNodes {
     }
 };
 
+// XCD-aware workgroup order: the dispatcher hands workgroups to the 8 XCDs
+// round-robin (b -> XCD b mod 8), each XCD with its own L2.  Renumbering
+// gives XCD x a contiguous range of the work instead of every eighth item,
+// so that the reconstruction windows and metric rows that neighbouring items
+// share are read into one L2.  Measured on the single-block sweeps: 2D
+// Double Mach Reflection 961x241 (LLC-resident) 62.3 -> 54.5 us per RK stage,
+// residual 45x33x29 23.9 -> 22.7 us, WENO-CU6 145x113x97 1350 -> 1318 us per
+// step, 256^3 WENO5 1-2%.  The batched sweeps keep the plain order: 48 body
+// blocks take the same time either way, and 24 serving blocks lost 2%.
+__device__ __forceinline__ long xcd_block(long b, long nb) {
+    const long per = nb / 8, rem = nb % 8, x = b % 8;
+    return x * per + (x < rem ? x : rem) + b / 8;
+}
+
 template <int PREC>
 using char_t = typename std::conditional<PREC == 1, float, double>::type;
 
@@ -637,7 +651,7 @@ void k_sweep_x(GeoK G, SchemeK sk, const double* __restrict__ met, const double*
     __shared__ XLds<DIM, NE> lds[4];
     XLds<DIM, NE>& L = lds[wave_id()];
     const unsigned total = ((unsigned)G.n[0] + 1) * (unsigned)G.n[1] * (unsigned)G.n[2];
-    const unsigned j = blockIdx.x * 4 + wave_id();
+    const unsigned j = (unsigned)xcd_block(blockIdx.x, gridDim.x) * 4 + wave_id();
     const unsigned W1 = (unsigned)G.xw - 1;
     // items of W faces start W - 1 apart; the last face starts none
     if ((unsigned long)j * W1 >= total - 1) return;
@@ -905,12 +919,12 @@ __global__ __launch_bounds__(256) FP_SWEEP_ATTR void k_sweep_wg(GeoK G, SchemeK 
     e.mode = MODE;
     const unsigned lblocks = (unsigned)(((long)G.n[0] * G.n[OTH] + 63) / 64);
     const int nd = G.n[DIR];
+    const unsigned wg = (unsigned)xcd_block(blockIdx.x, gridDim.x);
     if constexpr (!BALANCED) {
-        const int k0 = (int)(blockIdx.x / lblocks) * S;
-        sweep_wg_item<DIM, DIR, RECON, Y, PREC>(G, sk, met, qs, e, (int)(blockIdx.x % lblocks), k0, min(k0 + S, nd),
-                                                lds);
+        const int k0 = (int)(wg / lblocks) * S;
+        sweep_wg_item<DIM, DIR, RECON, Y, PREC>(G, sk, met, qs, e, (int)(wg % lblocks), k0, min(k0 + S, nd), lds);
     } else {
-        const unsigned u = blockIdx.x * (unsigned)S;
+        const unsigned u = wg * (unsigned)S;
         unsigned lineblk = u / (unsigned)nd;
         int k0 = (int)(u - lineblk * (unsigned)nd);
         for (int left = S; left > 0 && lineblk < lblocks; ++lineblk, k0 = 0) {

@@ -5,14 +5,6 @@
 
 namespace fpk {
 
-// XCD-aware workgroup order: the dispatcher hands workgroups to the 8 XCDs
-// round-robin (b -> XCD b mod 8), each XCD with its own L2.  Renumbering
-// gives XCD x a contiguous range of the work instead of every eighth item.
-__device__ __forceinline__ long xcd_block(long b, long nb) {
-    const long per = nb / 8, rem = nb % 8, x = b % 8;
-    return x * per + (x < rem ? x : rem) + b / 8;
-}
-
 // ---------------------------------------------------------------------------
 // symmetric conservative metrics (setup)
 // ---------------------------------------------------------------------------
