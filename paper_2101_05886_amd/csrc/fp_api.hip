@@ -618,7 +618,11 @@ size_t lnk_start_offset(int cap) { return lnk_offset(cap) + 256; }
 size_t lnk_arr_offset(int cap, int maxl) {
     return lnk_start_offset(cap) + align256(sizeof(long) * (size_t)(maxl + 1));
 }
-size_t part_size(int cap, int maxl) { return align256(lnk_arr_offset(cap, maxl) + sizeof(LinkK) * (size_t)maxl); }
+// the counters of the work lists, zero between launches and in every upload
+size_t next_offset(int cap, int maxl) { return align256(lnk_arr_offset(cap, maxl) + sizeof(LinkK) * (size_t)maxl); }
+size_t part_size(int cap, int maxl) {
+    return align256(next_offset(cap, maxl) + sizeof(unsigned) * kNextPitch * BK_KINDS);
+}
 
 // ghost-slab nodes of a link: g layers times the other axes' interior extents
 long link_nodes(const fp_grid& g, int axis) {
@@ -1332,6 +1336,7 @@ fp_status fp_batch_create(const fp_scheme* sch, int32_t max_blocks, fp_batch** o
         b->tab[p].start = reinterpret_cast<const long*>(base + start_offset());
         b->tab[p].blk = reinterpret_cast<const BBlock*>(base + blk_offset(max_blocks));
         b->tab[p].cap = max_blocks;
+        b->tab[p].next = reinterpret_cast<unsigned*>(base + next_offset(max_blocks, b->maxl));
         b->lnk_n[p] = reinterpret_cast<const int*>(base + lnk_offset(max_blocks));
         b->lnk_start[p] = reinterpret_cast<const long*>(base + lnk_start_offset(max_blocks));
         b->lnk[p] = reinterpret_cast<const LinkK*>(base + lnk_arr_offset(max_blocks, b->maxl));

@@ -207,11 +207,11 @@ hipError_t run_batch_stage(const BTab& t, const SchemeK& sk, int stage, const in
                            t.cap, sk, stage);
     if (only < 0 || only == BK_ETA)
         hipLaunchKernelGGL((kb_sweep_wg<DIM, 1, R, Y, P>), dim3(grid[1]), dim3(256), 0, s, t.nblk, t.start,
-                           t.blk, t.cap, sk, stage);
+                           t.blk, t.cap, sk, stage, t.next + BK_ETA * kNextPitch);
     if constexpr (DIM == 3)
         if (only < 0 || only == BK_ZETA)
             hipLaunchKernelGGL((kb_sweep_wg<3, 2, R, Y, P>), dim3(grid[2]), dim3(256), 0, s, t.nblk, t.start,
-                               t.blk, t.cap, sk, stage);
+                               t.blk, t.cap, sk, stage, t.next + BK_ZETA * kNextPitch);
     return hipGetLastError();
 }
 

@@ -772,11 +772,16 @@ __device__ __forceinline__ void wg_convert(WgLds<DIM, WIDE>& L, int slot, double
 // 8.29 FP32-mixed, and one of 128^3 with LU5 0.77 against 0.87.  Every thread
 // of the workgroup runs the same iterations and barriers.  A caller that reuses `L` for another item must
 // synchronise the workgroup first.
-template <int DIM, int DIR, int RECON, int Y, int PREC>
+// (the batched sweep has something to do when the item's first rows have
+// arrived)
+struct Nothing {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <int DIM, int DIR, int RECON, int Y, int PREC, typename FN = Nothing>
 __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
                                               const double* __restrict__ met, const double* qs,
                                               const EpiK& ep, int lineblk, int k0, int k1,
-                                              WgLds<DIM, wide_stencil(RECON, Y)>& L) {
+                                              WgLds<DIM, wide_stencil(RECON, Y)>& L, FN staged = FN()) {
     using W = WgLds<DIM, wide_stencil(RECON, Y)>;
     constexpr int NV = DIM + 2;
     constexpr int NMET = DIM == 3 ? 10 : 5;
@@ -832,6 +837,7 @@ __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
     for (int r = w; r < W::WIN; r += 4) load_row(tb + r);
     __builtin_amdgcn_s_waitcnt(0);
     asm volatile("" ::: "memory");
+    staged();
     for (int r = w; r < W::WIN; r += 4)
         if (tb + r <= tmax) wg_convert(L, r, gm1);
     __syncthreads();
@@ -1312,12 +1318,14 @@ struct BTab {
     const long* start;
     const BBlock* blk;
     int cap;
+    unsigned* next;  // per kind, kNextPitch apart: items taken beyond each workgroup's first
 };
+constexpr int kNextPitch = 32;
 
 // The order of the blocks within a kind's work list: position n of kind k
 // holds block kind_order(...)[n] (the list of a kind may put its blocks in
 // any order; the eta / zeta lists put the blocks with the longest items
-// first, so that the cyclic assignment of items to workgroups balances).
+// first, so that the last ones to be taken are short).
 // The array follows the prefix sums in the same table.
 __device__ __forceinline__ const int* kind_order(const long* t_start, int cap, int kind) {
     return reinterpret_cast<const int*>(t_start + BK_KINDS * (cap + 1)) + kind * cap;
@@ -1422,31 +1430,55 @@ __global__ __launch_bounds__(256) FP_XSWEEP_ATTR(PREC, RECON, Y) void kb_sweep_x
 }
 
 // Persistent batched eta / zeta sweep of one RK stage; the last direction
-// applies the RK3 update.
+// applies the RK3 update.  A long list is handed out: after its first item a
+// workgroup takes the next one nobody has, so none is left with a run of long
+// items at the end (48 body blocks, 20 million nodes: 9.30 -> 9.00 ms per
+// step).  The counter is asked beside the item's first loads and its answer
+// read when the item ends.  Every workgroup with a first item asks until it is
+// refused, `total` times in all, so the one that gets total - 1 is the last
+// and sets the counter back.  A short list is dealt out in turn: all
+// workgroups ask at once at first, 11 ns each, and few items follow to make up
+// for it (24 serving blocks, few items per workgroup, handed out: 4.84 ->
+// 4.93 ms for five steps).  The xi sweep's items are too small to be
+// handed out: the same serving blocks took 9.1 ms.
 template <int DIM, int DIR, int RECON, int Y, int PREC>
 __global__ __launch_bounds__(256) FP_SWEEP_ATTR void kb_sweep_wg(const int* __restrict__ t_nblk,
                                                                  const long* __restrict__ t_start,
                                                                  const BBlock* __restrict__ t_blk, int cap,
-                                                                 SchemeK sk, int stage) {
+                                                                 SchemeK sk, int stage, unsigned* next) {
     __shared__ WgLds<DIM, wide_stencil(RECON, Y)> lds;
+    __shared__ unsigned taken[2];
     constexpr int KIND = DIR == 1 ? BK_ETA : BK_ZETA;
     constexpr int MODE = DIR == DIM - 1 ? EPI_LAST_RK : EPI_MID;
     const int nblk = *t_nblk;
     const long* __restrict__ st = t_start + KIND * (cap + 1);
-    const long total = st[nblk];
+    const unsigned total = (unsigned)st[nblk];
     const int* __restrict__ ord = kind_order(t_start, cap, KIND);
-    int b = blockIdx.x < total ? find_block(st, nblk, blockIdx.x) : 0;
-    for (long item = blockIdx.x; item < total; item += gridDim.x) {
+    if (blockIdx.x >= total) return;
+    const bool handed = total > 6 * gridDim.x;
+    int b = find_block(st, nblk, blockIdx.x);
+    int cur = 0;
+    for (unsigned item = blockIdx.x; item < total; cur ^= 1) {
         b = advance_block(st, nblk, b, item);
         const BBlock& B = t_blk[ord[b]];
         const EpiK ep = stage_epi(B, stage, MODE, DIM);
         constexpr int OTH = DIR == 1 ? 2 : 1;
         const unsigned lblocks = (unsigned)(((long)B.G.n[0] * B.G.n[OTH] + 63) / 64);
-        const unsigned in = (unsigned)(item - st[b]);
+        const unsigned in = item - (unsigned)st[b];
         const int k0 = (int)(in / lblocks) * B.S[DIR];
+        unsigned c = 0;
+        if (handed && threadIdx.x == 0)
+            c = __hip_atomic_fetch_add(next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         sweep_wg_item<DIM, DIR, RECON, Y, PREC>(B.G, sk, B.met, stage_in(B, stage), ep, (int)(in % lblocks), k0,
-                                                min(k0 + B.S[DIR], B.G.n[DIR]), lds);
+                                                min(k0 + B.S[DIR], B.G.n[DIR]), lds, [&] {
+                                                    if (threadIdx.x != 0) return;
+                                                    taken[cur] = handed ? c + gridDim.x : item + gridDim.x;
+                                                    if (handed && c + 1 == total)
+                                                        __hip_atomic_store(next, 0u, __ATOMIC_RELAXED,
+                                                                           __HIP_MEMORY_SCOPE_AGENT);
+                                                });
         __syncthreads();  // the next item rewrites the LDS ring
+        item = (unsigned)__builtin_amdgcn_readfirstlane((int)taken[cur]);
     }
 }
 
