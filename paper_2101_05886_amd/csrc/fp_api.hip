@@ -202,9 +202,10 @@ SchemeK make_sk(const fp_scheme* s) {
 // they share with their neighbours, which LU5, nearest to the HBM bound,
 // feels first.  RK3 step, uniform and balanced: 145x113x97 WENO5 FP64 937
 // and 904 us, 160^3 2,328 and 2,276, 180x120x150 LU5 1,190 and 1,165; above
-// the limit 200^3 LU5 2,835 and 3,112, WENO5 mixed 3,855 and 3,903.  S = 3, one iteration, is the shortest segment, and
-// the best for blocks too small to fill the chip (a 45x33x29 residual: 30.2
-// us with S = 4, two iterations, 24.0 with 3).
+// the limit 200^3 LU5 2,835 and 3,112, WENO5 mixed 3,855 and 3,903.  S = 3,
+// one iteration, is the shortest segment, and the best for blocks too small to
+// fill the chip (a 45x33x29 residual: 30.2 us with S = 4, two iterations, 24.0
+// with 3).
 long piece_cost(long nodes) { return 2 * ((nodes + 4) / 4) + 1; }
 
 WgSplit plan_split(int nd, long lblocks, long longest) {

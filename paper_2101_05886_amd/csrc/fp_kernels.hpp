@@ -13,7 +13,7 @@
 // spilling.  The FP32-mixed xi sweeps of the six-point stencils (WENO5,
 // LU5, WENOCU6 with metrics of order up to 6) and the FP64 LU5 ones fit
 // three (at most 168 registers) and run at three: their LDS window buffers
-// allow it, the eta/zeta rings (72 KB per workgroup) do not; WENO7 and
+// allow it, the eta/zeta rings (79 KB per workgroup) do not; WENO7 and
 // eighth-order metrics would spill at three.
 #ifndef FP_SWEEP_ATTR
 #define FP_SWEEP_ATTR __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -336,7 +336,7 @@ __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane
 // entries; W is the largest width (at most 64) that fits NE entries.  The
 // sweeps that run three waves per SIMD stage NE = 88 entries (W = 64 still
 // for lines of 30 nodes and more): the workgroup's double buffers then take
-// 50 KB and three workgroups fit a CU's LDS; the others stage 128.
+// 53.5 KB and three workgroups fit a CU's LDS; the others stage 128.
 template <int DIM, int NE_>
 struct XLds {
     static constexpr int NE = NE_;          // staged entries per buffer

@@ -813,8 +813,7 @@ __global__ __launch_bounds__(256) void k_visc_div(GeoK G, const double* __restri
 // Bound by HBM: 352 algorithmic bytes per node.  The tile is 32 x 16: half
 // the halo of 64 x 8 and, with 160 nodes, no idle lanes.  Runs of 16 planes
 // (six more fill the registers) give a 160^3 block 800 workgroups; 32 planes
-// left a workgroup per CU.  160^3: fluxes 227 us, divergence 157 (3.9 and
-// 3.6 TB/s),
+// left a workgroup per CU.  160^3: fluxes 227 us, divergence 157,
 // against 329 and 200 with the halo and the tile loaded again from memory,
 // two barriers a plane, and no load ahead.
 constexpr int kVmI = 32, kVmJ = 16, kVmK = 16, kVmHI = kVmI + 6, kVmHJ = kVmJ + 6, kVmT = kVmI * kVmJ;

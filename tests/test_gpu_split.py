@@ -13,7 +13,7 @@ from tests import gpu_cases as G
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [(97, 90, 83), (130, 61, 70)])
+@pytest.mark.parametrize("n", [(97, 90, 83), (95, 88, 88), (102, 67, 109)])
 @pytest.mark.parametrize("recon", ["weno5", "linup5"])
 def test_balanced_split_matches_oracle_and_batch(recon, n):
     case = G.periodic_case(3, n, 4, state="noisy", seed=81)
