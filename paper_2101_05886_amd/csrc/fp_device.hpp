@@ -219,12 +219,22 @@ __device__ __forceinline__ float weno5(float a, float b, float c, float d, float
 //
 // FP64 forms the weights over one common denominator, so that a
 // reconstruction takes two reciprocals (each a quarter-rate instruction and
-// four Newton operations) instead of five or six.  The products span up to
-// 1e-300 .. 1e300: eps is floored far below any indicator of rounding noise.
+// four Newton operations) instead of five or six.  The weights depend on the
+// indicators' ratios alone, and products of six (five) indicators would
+// leave the range of FP64 from indicators of 1e51 (1e61): each window's
+// indicators are first brought to order one by a power of two, which rounds
+// nothing.  What is added to them then is 1e-50 (1e-60) of the largest, below
+// its rounding, and keeps the products off zero for any eps.
 // FP32 has no such range and takes a reciprocal per indicator.
 // RK3 steps with the indicators in values and a reciprocal each, and now:
-// FP64 WENOCU6 145x113x97 1.55 and 1.30 ms (2,248 and 1,914 FP64 operations
-// per face), FP32-mixed WENO7-M8 191x161x133 2.84 and 2.65 ms.
+// FP64 WENOCU6 145x113x97 1.55 and 1.29 ms (1.25 without the power of two),
+// FP32-mixed WENO7-M8 191x161x133 2.84 and 2.65 ms.
+
+// 2^-k for x in [2^k, 2^(k+1)), x > 0
+__device__ __forceinline__ double pow2_rcp(double x) {
+    const unsigned long long e = __builtin_bit_cast(unsigned long long, x) >> 52 & 0x7ff;
+    return __builtin_bit_cast(double, (0x7feull - e) << 52);
+}
 
 // one indicator of WENO7: a quadratic form in three consecutive differences
 template <typename T>
@@ -242,11 +252,18 @@ __device__ __forceinline__ T weno7(const T (&v)[7], T eps) {
     const T a = v[0], b = v[1], c = v[2], d = v[3], e = v[4], f = v[5], g = v[6];
     const T f0 = b - a, f1 = c - b, f2 = d - c, f3 = e - d, f4 = f - e, f5 = g - f;
     constexpr bool F64 = sizeof(T) == 8;
-    const T ep = F64 ? fmax(eps, T(1e-50)) : eps;
-    T b0 = form3<T>(f0, f1, f2, T(547), T(-2788), T(1854), T(3708), T(-5188), T(2107), ep);
-    T b1 = form3<T>(f1, f2, f3, T(267), T(-1108), T(494), T(1468), T(-1428), T(547), ep);
-    T b2 = form3<T>(f2, f3, f4, T(547), T(-1428), T(494), T(1468), T(-1108), T(267), ep);
-    T b3 = form3<T>(f3, f4, f5, T(2107), T(-5188), T(1854), T(3708), T(-2788), T(547), ep);
+    T b0 = form3<T>(f0, f1, f2, T(547), T(-2788), T(1854), T(3708), T(-5188), T(2107), eps);
+    T b1 = form3<T>(f1, f2, f3, T(267), T(-1108), T(494), T(1468), T(-1428), T(547), eps);
+    T b2 = form3<T>(f2, f3, f4, T(547), T(-1428), T(494), T(1468), T(-1108), T(267), eps);
+    T b3 = form3<T>(f3, f4, f5, T(2107), T(-5188), T(1854), T(3708), T(-2788), T(547), eps);
+    if constexpr (F64) {
+        // b0 + b3 sees all six differences: b1 and b2 are below 6 times it
+        const T sc = pow2_rcp(b0 + b3), lo = T(1e-50);
+        b0 = fma(b0, sc, lo);
+        b1 = fma(b1, sc, lo);
+        b2 = fma(b2, sc, lo);
+        b3 = fma(b3, sc, lo);
+    }
     b0 *= b0;
     b1 *= b1;
     b2 *= b2;
@@ -294,7 +311,6 @@ __device__ __forceinline__ T wenocu6(const T (&v)[6], T eps) {
     const T s0 = T(3) * f2 - f1, s1 = f2 + f3, s2 = T(3) * f3 - f4;
     const T k13 = T(13.0 / 3.0);
     constexpr bool F64 = sizeof(T) == 8;
-    const T ep = F64 ? fmax(eps, T(1e-60)) : eps;
     const T b0 = k13 * t0 * t0 + s0 * s0;
     const T b1 = k13 * t1 * t1 + s1 * s1;
     const T b2 = k13 * t2 * t2 + s2 * s2;
@@ -306,8 +322,22 @@ __device__ __forceinline__ T wenocu6(const T (&v)[6], T eps) {
                  G2 * (G2 * T(13.0 / 12.0) + D4 * T(7.0 / 40.0)) +
                  G3 * (G3 * T(1043.0 / 960.0) + D5 * T(4709.0 / 26880.0)) +
                  D4 * D4 * T(87617.0 / 20160.0) + D5 * D5 * T(50467427.0 / 11612160.0);
-    const T tau = b6 - (b0 + T(4) * b1 + b2) * T(1.0 / 6.0);
-    const T e0 = b0 + ep, e1 = b1 + ep, e2 = b2 + ep, e3 = b6 + ep;
+    T tau = b6 - (b0 + T(4) * b1 + b2) * T(1.0 / 6.0);
+    T e0, e1, e2, e3;
+    if constexpr (F64) {
+        // beta6 sees all five differences: the others are below 3 times it
+        const T sc = pow2_rcp(b6 + eps), es = fma(eps, sc, T(1e-60));
+        tau *= sc;
+        e0 = fma(b0, sc, es);
+        e1 = fma(b1, sc, es);
+        e2 = fma(b2, sc, es);
+        e3 = fma(b6, sc, es);
+    } else {
+        e0 = b0 + eps;
+        e1 = b1 + eps;
+        e2 = b2 + eps;
+        e3 = b6 + eps;
+    }
     const T m = fmin(fmin(e0, e1), fmin(e2, e3));
     const T mt = m + fabs(tau);
     if constexpr (F64) {
