@@ -295,8 +295,11 @@ fp_status fp_profile_step(const fp_grid *grid, const fp_scheme *scheme, const fp
  * at a stated CFL number (Sec. 4.2.1: 0.6) without the rule being printed;
  * this is the convective limit in index space, the characteristic speeds of
  * the transformed equations of Sec. 2.1 (|U_d| + c |grad xi_d| along each
- * index direction) summed over the directions.  FP_EINVAL on a bad grid,
- * scheme or pointer; cfl must be positive. */
+ * index direction) summed over the directions.  A non-physical node (NaN or
+ * negative pressure) is left out beside valid ones; dt is NaN where a run of
+ * 256 nodes (of the interior, i fastest, counted from its first) has no valid
+ * one (fp_check_state finds single ones).  FP_EINVAL on a bad grid, scheme or
+ * pointer; cfl must be positive. */
 fp_status fp_max_dt(const fp_grid *grid, const fp_scheme *scheme, const double *met,
                     const double *q, double cfl, double *dt_dev, void *stream);
 

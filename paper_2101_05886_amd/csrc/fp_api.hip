@@ -1250,9 +1250,11 @@ fp_status fp_max_dt(const fp_grid* g, const fp_scheme* sch, const double* met, c
     const long tot = (long)G.n[0] * G.n[1] * G.n[2];
     unsigned long long* bits = reinterpret_cast<unsigned long long*>(dt_dev);
     hipLaunchKernelGGL(k_dt_init, dim3(1), dim3(1), 0, s, bits);
-    // (each block folds its maximum in by an atomic, and those serialise:
+    // at most 2048 workgroups of four waves, which take the same number of runs
+    // within one (each folds its maximum in by an atomic, and those serialise:
     // about 11 ns each)
-    const unsigned blocks = (unsigned)std::min((tot + 255) / 256, 2048L);
+    const long runs = (tot + kDtRun - 1) / kDtRun, each = (runs + 8191) / 8192;
+    const unsigned blocks = (unsigned)((runs + 4 * each - 1) / (4 * each));
     if (g->ndim == 3)
         hipLaunchKernelGGL(k_dt_reduce<3>, dim3(blocks), dim3(256), 0, s, G, sch->gamma, met, q, bits);
     else

@@ -1023,51 +1023,68 @@ __global__ __launch_bounds__(kVmT) void k_visc_div3(GeoK G, const double* __rest
 
 __global__ void k_dt_init(unsigned long long* bits) { *bits = 0ull; }
 
-// Grid-stride over the interior nodes, one atomic per workgroup (non-negative
-// doubles order as their bit patterns do).  Bound by HBM: 160x144x150 takes
-// 79 us (15 arrays read, 415 MB), 170 with a workgroup and an atomic per
-// 256 nodes.
+// sum_d (|s_d . u| + c |s_d|) (1/J)^{-1} at interior node t (0 past the last)
+template <int DIM>
+__device__ __forceinline__ double dt_node(const GeoK& G, double gamma, const double* __restrict__ met,
+                                          const double* __restrict__ q, long t, long tot) {
+    constexpr int NV = DIM + 2, NMET = DIM == 3 ? 10 : 5;
+    if (t >= tot) return 0.0;
+    const long r = t / G.n[0];
+    const int i = (int)(t - r * G.n[0]);
+    const int j = (int)(r % G.n[1]);
+    const int k = (int)(r / G.n[1]);
+    const long off = G.base + i + j * G.sd[1] + (long)k * G.sd[2];
+    const double rho = q[off];
+    double u[DIM], m2 = 0.0;
+    for (int c = 0; c < DIM; ++c) {
+        u[c] = q[(1 + c) * G.vol + off] / rho;
+        m2 += q[(1 + c) * G.vol + off] * u[c];
+    }
+    const double p = (gamma - 1.0) * (q[(NV - 1) * G.vol + off] - 0.5 * m2);
+    const double cs = sqrt(gamma * p / rho);
+    double sum = 0.0;
+    for (int d = 0; d < DIM; ++d) {
+        double su = 0.0, ss = 0.0;
+        for (int c = 0; c < DIM; ++c) {
+            const double s = met[(d * DIM + c) * G.vol + off];
+            su += s * u[c];
+            ss += s * s;
+        }
+        sum += fabs(su) + cs * sqrt(ss);
+    }
+    return sum / met[(NMET - 1) * G.vol + off];
+}
+
+// A wave takes runs of 256 interior nodes (four per lane).  fmax drops the
+// NaN of a non-physical node beside others, but a run of nothing else stays
+// NaN, whose bits are above every number's (non-negative doubles order as
+// their bit patterns do), and the state's dt is NaN.  Bound by HBM:
+// 160x144x150 (15 arrays read, 415 MB) takes 86 us, 80 where waves do not keep
+// to runs (and lose their NaN), 170 with a workgroup and an atomic per run.
+constexpr int kDtRun = 256;
 template <int DIM>
 __global__ __launch_bounds__(256) void k_dt_reduce(GeoK G, double gamma,
                                                     const double* __restrict__ met,
                                                     const double* __restrict__ q,
                                                     unsigned long long* bits) {
-    constexpr int NV = DIM + 2, NMET = DIM == 3 ? 10 : 5;
     const long tot = (long)G.n[0] * G.n[1] * G.n[2];
-    double val = 0.0;
-    for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < tot; t += (long)gridDim.x * blockDim.x) {
-        const long r = t / G.n[0];
-        const int i = (int)(t - r * G.n[0]);
-        const int j = (int)(r % G.n[1]);
-        const int k = (int)(r / G.n[1]);
-        const long off = G.base + i + j * G.sd[1] + (long)k * G.sd[2];
-        const double rho = q[off];
-        double u[DIM], m2 = 0.0;
-        for (int c = 0; c < DIM; ++c) {
-            u[c] = q[(1 + c) * G.vol + off] / rho;
-            m2 += q[(1 + c) * G.vol + off] * u[c];
-        }
-        const double p = (gamma - 1.0) * (q[(NV - 1) * G.vol + off] - 0.5 * m2);
-        const double cs = sqrt(gamma * p / rho);
-        double sum = 0.0;
-        for (int d = 0; d < DIM; ++d) {
-            double su = 0.0, ss = 0.0;
-            for (int c = 0; c < DIM; ++c) {
-                const double s = met[(d * DIM + c) * G.vol + off];
-                su += s * u[c];
-                ss += s * s;
-            }
-            sum += fabs(su) + cs * sqrt(ss);
-        }
-        val = fmax(val, sum / met[(NMET - 1) * G.vol + off]);
-    }
+    const int lane = threadIdx.x & 63;
+    unsigned long long most = 0;
+    for (long t = ((long)blockIdx.x * 4 + wave_id()) * kDtRun; t < tot; t += (long)gridDim.x * 4 * kDtRun) {
+        double val = dt_node<DIM>(G, gamma, met, q, t + lane, tot);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) val = fmax(val, __shfl_xor(val, o));
-    __shared__ double red[4];
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = val;
+        for (int h = 1; h < kDtRun / 64; ++h) val = fmax(val, dt_node<DIM>(G, gamma, met, q, t + 64 * h + lane, tot));
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) val = fmax(val, __shfl_xor(val, o));
+        most = max(most, (unsigned long long)__double_as_longlong(val));
+    }
+    __shared__ unsigned long long red[4];
+    if (lane == 0) red[threadIdx.x >> 6] = most;
     __syncthreads();
-    if (threadIdx.x == 0)
-        atomicMax(bits, (unsigned long long)__double_as_longlong(fmax(fmax(red[0], red[1]), fmax(red[2], red[3]))));
+    if (threadIdx.x == 0) {
+        most = max(max(red[0], red[1]), max(red[2], red[3]));
+        if (most > __hip_atomic_load(bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(bits, most);
+    }
 }
 
 __global__ void k_dt_final(unsigned long long* bits, double cfl) {
