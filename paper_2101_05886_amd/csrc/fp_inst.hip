@@ -64,7 +64,7 @@ void launch_glf(const SweepArgs& a, hipStream_t s) {
     }
     const long bpd = (most + 511) / 512 < 128 ? (most + 511) / 512 : 128;
     hipLaunchKernelGGL((k_glf<DIM, Y, R == 2 ? 3 : 2>), dim3((unsigned)(bpd * DIM)), dim3(512), 0, s, a.G,
-                       a.sk.gamma - 1.0, a.sk.sg, a.met, a.qs, set, next, (int)bpd, a.glf_time, a.time_dt);
+                       a.sk.gamma, a.met, a.qs, set, next, (int)bpd, a.glf_time, a.time_dt);
 }
 
 // resident workgroups of a kernel on the current device (queried once)

@@ -1148,18 +1148,22 @@ __device__ __forceinline__ void time_advance(double* T, double dt) {
     T[0] = T[1] + n * dt;
 }
 
-// velocity and sound speed of the node at `off`
+// velocity and sound speed of the node at `off` (NaN where the pressure is
+// negative: such a node counts for the class u_n alone, as fmax drops NaN).
+// One divided node serves up to six faces: plain divisions and roots here.
 template <int DIM>
-__device__ __forceinline__ void glf_node(const double* __restrict__ q, long vol, long off, double gm1, double sg,
-                                         double* u, double& cs) {
-    double qv[DIM + 2];
+__device__ __forceinline__ void glf_node(const double* __restrict__ q, long vol, long off, double gamma, double* u,
+                                         double& cs) {
+    const double rho = q[off];
+    double k2 = 0.0;
 #pragma unroll
-    for (int v = 0; v < DIM + 2; ++v) qv[v] = q[v * vol + off];
-    Prim<DIM> P;
-    to_prim<DIM>(qv, gm1, P);
-#pragma unroll
-    for (int c = 0; c < DIM; ++c) u[c] = P.u[c];
-    cs = sg * fmax(P.ct, 0.0);
+    for (int c = 0; c < DIM; ++c) {
+        const double mc = q[(1 + c) * vol + off];
+        u[c] = mc / rho;
+        k2 += mc * u[c];
+    }
+    const double p = (gamma - 1.0) * (q[(DIM + 1) * vol + off] - 0.5 * k2);
+    cs = sqrt(gamma * p / rho);
 }
 
 // The largest local Lax-Friedrichs speed over every face of every direction
@@ -1181,14 +1185,15 @@ __device__ __forceinline__ void glf_node(const double* __restrict__ q, long vol,
 // into `set` with one integer atomic max per class (non-negative doubles
 // order as their bit patterns do): few large blocks, since atomics on one
 // cache line serialise.  Four faces a thread evaluate 2.25 nodes per face
-// (two faces: 3.5); with the primitives of the sweeps in place of divisions,
-// 14.0 us against 15.1 on a 961x241 grid, where launch, load latency and the
-// atomics are the rest.  Block 0 also zeroes `next` (the set the following
+// (two faces: 3.5): 13.9 us against 15.7 on a 961x241 grid, where launch, load
+// latency and the atomics are the rest.  (The one-step reciprocals and roots
+// of the faces' basis would take 13.4: not worth their bits in a speed that
+// every face of the block takes as its floor.)  Block 0 also zeroes `next` (the set the following
 // reduction folds into; NULL: none) and, in the last stage of a captured
 // step, advances the device time `T` that the next step starts from (NULL:
 // none; a launch of its own took 4 us of a 190 us step).
 template <int DIM, int Y, int LO>
-__global__ __launch_bounds__(512) void k_glf(GeoK G, double gm1, double sg, const double* __restrict__ met,
+__global__ __launch_bounds__(512) void k_glf(GeoK G, double gamma, const double* __restrict__ met,
                                               const double* __restrict__ q, unsigned long long* set,
                                               unsigned long long* next, int bpd, double* T, double dt) {
     constexpr int NMET = DIM == 3 ? 10 : 5;
@@ -1223,7 +1228,7 @@ __global__ __launch_bounds__(512) void k_glf(GeoK G, double gm1, double sg, cons
             // nodes past the last face's stencil are never read: clamp them
             int p = min(f0 - LO + j, nd + LO);
             if (per) p = p < 0 ? p + nd : (p >= nd ? p - nd : p);
-            glf_node<DIM>(q, G.vol, line + (long)p * sdd, gm1, sg, u[j], cs[j]);
+            glf_node<DIM>(q, G.vol, line + (long)p * sdd, gamma, u[j], cs[j]);
         }
 #pragma unroll
         for (int j = 0; j < kGlfSeg; ++j) {
@@ -1243,11 +1248,11 @@ __global__ __launch_bounds__(512) void k_glf(GeoK G, double gm1, double sg, cons
             double s2 = 0.0;
 #pragma unroll
             for (int c = 0; c < DIM; ++c) s2 += sf[c] * sf[c];
-            const double isn = drsq1(s2);  // as in the face's basis (roe)
-            const double sigma = s2 * isn * drcp1(Vf);
+            const double sn = sqrt(s2);
+            const double sigma = sn / Vf;
             double n[DIM];
 #pragma unroll
-            for (int c = 0; c < DIM; ++c) n[c] = sf[c] * isn;
+            for (int c = 0; c < DIM; ++c) n[c] = sf[c] / sn;
 #pragma unroll
             for (int m = 0; m <= 2 * LO + 1; ++m) {
                 double un = 0.0;
