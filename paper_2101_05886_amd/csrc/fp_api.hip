@@ -181,7 +181,7 @@ SchemeK make_sk(const fp_scheme* s) {
     k.eps = s->weno_eps;
     k.reform = s->reformulated;
     k.sg = std::sqrt(s->gamma);
-    k.igm1 = 1.0 / (s->gamma - 1.0);
+    k.gg = s->gamma / (s->gamma - 1.0);
     k.glf = nullptr;  // bound by bind_speeds once the arguments are checked
     return k;
 }

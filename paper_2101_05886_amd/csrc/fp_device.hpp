@@ -4,8 +4,8 @@
 // One face i+1/2 of one grid line is evaluated by one lane.  The lane reads
 // the stencil nodes through a loader (slot r = 0..7 <-> node i-3+r) phase by
 // phase, so that only the values of the current phase are live in registers.
-// A node comes as primitives (Prim), which the sweeps form once per node
-// instead of once per face that uses it:
+// A node comes with its quotients and roots taken (Prim), which the sweeps do
+// once per node instead of once per face that uses it:
 //   A. cell-face 1/J, metrics and Q~ = Q/J by the central interpolation of
 //      the metric order Y; reference state Q* = Q~_f/(1/J)_f and reference
 //      face flux F~*_f = F(Q*) s_f                                    [FP64]
@@ -27,7 +27,7 @@ struct SchemeK {
     double eps;
     int reform;  // 1: reference state subtracted (the paper); 0: standard scheme
     double sg;   // sqrt(gamma)
-    double igm1; // 1 / (gamma - 1)
+    double gg;   // gamma / (gamma - 1)
     // floor of the Lax-Friedrichs speeds of the sweep direction (u_n - c,
     // u_n, u_n + c): the face takes max(local speed, floor).  With global
     // speeds the floor is the block's largest local speed, so the face takes
@@ -97,14 +97,40 @@ __device__ __forceinline__ double vsqrt<double>(double x) { return sqrt(x); }
 template <>
 __device__ __forceinline__ float vsqrt<float>(float x) { return fast_sqrt(x); }
 
-// Primitives of a node: density, velocity, specific total energy E/rho and
-// the signed thermal speed ct = sign(r) sqrt|r|, r = p/rho, so that
-// r = ct |ct|, p = rho ct |ct| also where p < 0, and the sound speed is
-// sqrt(gamma) ct for r > 0, else 0.
+// Sums of two products name the one that is fused: left to the compiler, the
+// choice varies with the code around, and the sweeps that share the functions
+// below must agree (a face's flux is the same number in each of them).
+// prod2 = a b + c d with c d rounded.
+template <typename T>
+__device__ __forceinline__ T prod2(T a, T b, T c, T d) {
+    return fma(a, b, c * d);
+}
+
+// A node as the faces read it: density, velocity, total energy and, from
+// loaders that hold it (LD::CT), the signed thermal speed ct = sign(r) sqrt|r|,
+// r = p/rho, so that the sound speed is sqrt(gamma) ct for r > 0, else 0.
+// The velocity is rounded once (to_prim), so that rho u is the momentum to the
+// last bit or nearly so; energy and pressure see no roots or quotients.  The
+// residual's FP64 error is then that of nodes kept as conserved values, or
+// lower; with E/rho and rho ct |ct| in their places it was 16 to 42% higher.
 template <int DIM>
 struct Prim {
-    double rho, u[DIM], e, ct;
+    double rho, u[DIM], E, ct;
 };
+
+// momentum (a product on its own: contracted into a difference it would keep
+// the velocity's rounding) and pressure of a node
+template <int DIM>
+__device__ __forceinline__ double momentum(const Prim<DIM>& P, int c) {
+    return fma(P.rho, P.u[c], 0.0);
+}
+template <int DIM>
+__device__ __forceinline__ double pressure(const Prim<DIM>& P, double gm1) {
+    double m2 = 0.0;
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) m2 = fma(momentum(P, c), P.u[c], m2);
+    return gm1 * fma(-0.5, m2, P.E);
+}
 
 // sign(x) sqrt|x|: Newton steps on the hardware estimate of 1/sqrt|x| and
 // one residual correction (Goldschmidt's form), within a rounding or two
@@ -127,13 +153,14 @@ __device__ __forceinline__ void to_prim(const double (&q)[DIM + 2], double gm1, 
     const double ir = drcp(q[0]);
     double k2 = 0.0;
     P.rho = q[0];
+    P.E = q[DIM + 1];
 #pragma unroll
     for (int c = 0; c < DIM; ++c) {
-        P.u[c] = q[1 + c] * ir;
+        const double u = q[1 + c] * ir;
+        P.u[c] = fma(fma(-q[0], u, q[1 + c]), ir, u);
         k2 = fma(P.u[c], P.u[c], k2);
     }
-    P.e = q[DIM + 1] * ir;
-    P.ct = signed_sqrt(gm1 * fma(-0.5, k2, P.e));
+    P.ct = signed_sqrt(gm1 * fma(P.E, ir, -0.5 * k2));
 }
 
 // central face interpolation weights of order Y on slot r (node i in slot 3)
@@ -191,9 +218,9 @@ __device__ __forceinline__ double weno5(double a, double b, double c, double d, 
 // than c and d and round coarser: the difference form of the FP64 path raises
 // the FP32 error of the flux 1.3 to 1.5 times.
 __device__ __forceinline__ float weno5(float a, float b, float c, float d, float e, float eps16) {
-    const float c0 = 0.2f * a - 0.7f * b + 1.1f * c;
-    const float c1 = -0.6f * b + 3.0f * c + 1.2f * d;
-    const float c2 = 0.6f * c + 1.5f * d - 0.3f * e;
+    const float c0 = fma(1.1f, c, prod2(-0.7f, b, 0.2f, a));
+    const float c1 = fma(1.2f, d, prod2(3.0f, c, -0.6f, b));
+    const float c2 = fma(-0.3f, e, prod2(1.5f, d, 0.6f, c));
     const float t0 = a - 2.0f * b + c, s0 = a - 4.0f * b + 3.0f * c;
     const float t1 = b - 2.0f * c + d, s1 = d - b;
     const float t2 = c - 2.0f * d + e, s2 = 3.0f * c - 4.0f * d + e;
@@ -204,7 +231,7 @@ __device__ __forceinline__ float weno5(float a, float b, float c, float d, float
     const float r0 = fast_rcp(d0 * d0), r1 = fast_rcp(d1 * d1), r2 = fast_rcp(d2 * d2);
     const float num = fmaf(r0, c0, fmaf(r1, c1, r2 * c2));
     const float den = fmaf(r0, 0.6f, fmaf(r1, 3.6f, r2 * 1.8f));
-    return num * fast_rcp(den);
+    return fma(num, fast_rcp(den), 0.0f);
 }
 
 // The reconstructions below take twice the split values; their indicators
@@ -239,7 +266,7 @@ __device__ __forceinline__ double pow2_rcp(double x) {
 // one indicator of WENO7: a quadratic form in three consecutive differences
 template <typename T>
 __device__ __forceinline__ T form3(T f1, T f2, T f3, T c11, T c12, T c13, T c22, T c23, T c33, T eps) {
-    return f1 * (c11 * f1 + c12 * f2 + c13 * f3) + (f2 * (c22 * f2 + c23 * f3) + (c33 * f3 * f3 + eps));
+    return fma(f1, fma(c13, f3, prod2(c12, f2, c11, f1)), fma(f2, prod2(c23, f3, c22, f2), fma(c33 * f3, f3, eps)));
 }
 
 // WENO7-JS of a 7-point window v[0..6] (face between v[3] and v[4], upwind
@@ -271,18 +298,20 @@ __device__ __forceinline__ T weno7(const T (&v)[7], T eps) {
     if constexpr (F64) {
         const T b01 = b0 * b1, b23 = b2 * b3;
         const T a0 = b1 * b23, a1 = b0 * (T(12) * b23), a2 = b3 * (T(18) * b01), a3 = b2 * (T(4) * b01);
-        const T q0 = T(3) * f0 - T(10) * f1 + T(13) * f2;  // 12 (q_k - d)
-        const T q1 = T(4) * f2 + T(3) * f3 - f1;
+        const T q0 = fma(T(13), f2, prod2(T(-10), f1, T(3), f0));  // 12 (q_k - d)
+        const T q1 = prod2(T(3), f3, T(4), f2) - f1;
         const T q2 = T(6) * f3 + f2 - f4;
-        const T q3 = T(9) * f3 - T(4) * f4 + f5;
-        return fma(a0 * q0 + a1 * q1 + a2 * q2 + a3 * q3, rcp<T>(T(12) * (a0 + a1 + a2 + a3)), d);
+        const T q3 = prod2(T(-4), f4, T(9), f3) + f5;
+        const T num = fma(a3, q3, fma(a2, q2, prod2(a1, q1, a0, q0)));
+        return fma(num, rcp<T>(T(12) * (a0 + a1 + a2 + a3)), d);
     } else {
-        const T q0 = T(-3) * a + T(13) * b - T(23) * c + T(25) * d;
+        const T q0 = fma(T(25), d, fma(T(-23), c, prod2(T(13), b, T(-3), a)));
         const T q1 = b - T(5) * c + T(13) * d + T(3) * e;
         const T q2 = -c + T(7) * d + T(7) * e - f;
-        const T q3 = T(3) * d + T(13) * e - T(5) * f + g;
+        const T q3 = fma(T(-5), f, prod2(T(13), e, T(3), d)) + g;
         const T a0 = rcp<T>(b0), a1 = T(12) * rcp<T>(b1), a2 = T(18) * rcp<T>(b2), a3 = T(4) * rcp<T>(b3);
-        return (a0 * q0 + a1 * q1 + a2 * q2 + a3 * q3) * rcp<T>(T(12) * (a0 + a1 + a2 + a3));
+        const T num = fma(a3, q3, fma(a2, q2, prod2(a1, q1, a0, q0)));
+        return fma(num, rcp<T>(T(12) * (a0 + a1 + a2 + a3)), T(0));
     }
 }
 
@@ -311,17 +340,18 @@ __device__ __forceinline__ T wenocu6(const T (&v)[6], T eps) {
     const T s0 = T(3) * f2 - f1, s1 = f2 + f3, s2 = T(3) * f3 - f4;
     const T k13 = T(13.0 / 3.0);
     constexpr bool F64 = sizeof(T) == 8;
-    const T b0 = k13 * t0 * t0 + s0 * s0;
-    const T b1 = k13 * t1 * t1 + s1 * s1;
-    const T b2 = k13 * t2 * t2 + s2 * s2;
+    const T b0 = prod2(s0, s0, k13 * t0, t0);
+    const T b1 = prod2(s1, s1, k13 * t1, t1);
+    const T b2 = prod2(s2, s2, k13 * t2, t2);
     const T D4 = u2 - u1, D5 = (u3 - u2) - D4;
     const T G1 = s1 - T(341.0 / 2880.0) * u1 - T(1118.0 / 2880.0) * u2 + T(259.0 / 2880.0) * u3;  // 2 D1
-    const T G2 = T(2) * t1 - T(0.25) * D4;                                                          // 2 D2
-    const T G3 = T(5.0 / 12.0) * u1 + T(26.0 / 12.0) * u2 - T(7.0 / 12.0) * u3;                     // 2 D3
-    const T b6 = G1 * (G1 + G3 * T(1.0 / 12.0) + D5 * T(1.0 / 480.0)) +
-                 G2 * (G2 * T(13.0 / 12.0) + D4 * T(7.0 / 40.0)) +
-                 G3 * (G3 * T(1043.0 / 960.0) + D5 * T(4709.0 / 26880.0)) +
-                 D4 * D4 * T(87617.0 / 20160.0) + D5 * D5 * T(50467427.0 / 11612160.0);
+    const T G2 = prod2(T(-0.25), D4, T(2), t1);                                                        // 2 D2
+    const T G3 = fma(T(-7.0 / 12.0), u3, prod2(T(26.0 / 12.0), u2, T(5.0 / 12.0), u1));  // 2 D3
+    const T h1 = G1 + G3 * T(1.0 / 12.0) + D5 * T(1.0 / 480.0);
+    const T h2 = prod2(D4, T(7.0 / 40.0), G2, T(13.0 / 12.0));
+    const T h3 = prod2(D5, T(4709.0 / 26880.0), G3, T(1043.0 / 960.0));
+    const T b6 = fma(D5 * D5, T(50467427.0 / 11612160.0),
+                     fma(D4 * D4, T(87617.0 / 20160.0), fma(G3, h3, prod2(G2, h2, G1, h1))));
     T tau = b6 - (b0 + T(4) * b1 + b2) * T(1.0 / 6.0);
     T e0, e1, e2, e3;
     if constexpr (F64) {
@@ -348,20 +378,22 @@ __device__ __forceinline__ T wenocu6(const T (&v)[6], T eps) {
         const T x01 = x * e23, x23 = x * e01;
         const T w0 = fma(x01, e1, sC), w1 = fma(x01, e0, sC), w2 = fma(x23, e3, sC), w3 = fma(x23, e2, sC);
         const T a0 = w0 * w0, a1 = T(9) * (w1 * w1), a2 = T(9) * (w2 * w2), a3 = w3 * w3;
-        const T q0 = T(5) * f2 - T(2) * f1, q1 = T(2) * f3 + f2;  // 6 (q_k - c)
-        const T q2 = T(4) * f3 - f4, q3 = T(6) * f3 - T(5) * f4 + T(2) * f5;
-        return fma(a0 * q0 + a1 * q1 + a2 * q2 + a3 * q3, rcp<T>(T(6) * (a0 + a1 + a2 + a3)), c);
+        const T q0 = prod2(T(-2), f1, T(5), f2), q1 = T(2) * f3 + f2;  // 6 (q_k - c)
+        const T q2 = T(4) * f3 - f4, q3 = fma(T(2), f5, prod2(T(-5), f4, T(6), f3));
+        const T num = fma(a3, q3, fma(a2, q2, prod2(a1, q1, a0, q0)));
+        return fma(num, rcp<T>(T(6) * (a0 + a1 + a2 + a3)), c);
     } else {
         const T ig = rcp<T>(mt);
         const T sC = T(20) * (m * ig), st = tau * ig;
-        const T w0 = sC + st * (m * rcp<T>(e0)), w1 = sC + st * (m * rcp<T>(e1));
-        const T w2 = sC + st * (m * rcp<T>(e2)), w3 = sC + st * (m * rcp<T>(e3));
+        const T w0 = fma(st, m * rcp<T>(e0), sC), w1 = fma(st, m * rcp<T>(e1), sC);
+        const T w2 = fma(st, m * rcp<T>(e2), sC), w3 = fma(st, m * rcp<T>(e3), sC);
         const T a0 = w0 * w0, a1 = T(9) * (w1 * w1), a2 = T(9) * (w2 * w2), a3 = w3 * w3;
-        const T q0 = T(2) * a - T(7) * b + T(11) * c;
+        const T q0 = fma(T(11), c, prod2(T(-7), b, T(2), a));
         const T q1 = -b + T(5) * c + T(2) * d;
-        const T q2 = T(2) * c + T(5) * d - e;
-        const T q3 = T(11) * d - T(7) * e + T(2) * f;
-        return (a0 * q0 + a1 * q1 + a2 * q2 + a3 * q3) * rcp<T>(T(6) * (a0 + a1 + a2 + a3));
+        const T q2 = prod2(T(5), d, T(2), c) - e;
+        const T q3 = fma(T(2), f, prod2(T(-7), e, T(11), d));
+        const T num = fma(a3, q3, fma(a2, q2, prod2(a1, q1, a0, q0)));
+        return fma(num, rcp<T>(T(6) * (a0 + a1 + a2 + a3)), T(0));
     }
 }
 
@@ -420,7 +452,7 @@ __device__ __forceinline__ void face_ref(const LD& ld, const SchemeK& sk, FaceRe
     }
     R.Fts[0] = R.Qs[0] * U;
 #pragma unroll
-    for (int c = 0; c < DIM; ++c) R.Fts[1 + c] = R.Qs[1 + c] * U + R.ps * sf[c];
+    for (int c = 0; c < DIM; ++c) R.Fts[1 + c] = prod2(R.ps, sf[c], R.Qs[1 + c], U);
     R.Fts[E] = (R.Qs[E] + R.ps) * U;
     R.s2 = s2;
 }
@@ -449,19 +481,30 @@ __device__ __forceinline__ void roe(const LD& ld, const SchemeK& sk, const FaceR
     Prim<DIM> L, Q;
     ld.prim(3, L);
     ld.prim(4, Q);
-    const double HL = fma(L.ct, fabs(L.ct), L.e), HR = fma(Q.ct, fabs(Q.ct), Q.e);
+    // H = |u|^2/2 + gamma/(gamma - 1) p/rho
+    auto enthalpy = [&](const Prim<DIM>& P) {
+        if constexpr (LD::CT) {
+            double k2 = 0.0;
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) k2 = fma(P.u[c], P.u[c], k2);
+            return fma(sk.gg * P.ct, fabs(P.ct), 0.5 * k2);
+        } else {
+            return (P.E + pressure(P, gm1)) * drcp(P.rho);
+        }
+    };
+    const double HL = enthalpy(L), HR = enthalpy(Q);
     const T wL = T(L.rho) * rsq1<T>(T(L.rho)), wR = T(Q.rho) * rsq1<T>(T(Q.rho));
     const T iwr = rcp1<T>(wL + wR);
     T q2 = T(0), un = T(0);
 #pragma unroll
     for (int c = 0; c < DIM; ++c) {
-        S.uh[c] = (wL * T(L.u[c]) + wR * T(Q.u[c])) * iwr;
+        S.uh[c] = prod2(wR, T(Q.u[c]), wL, T(L.u[c])) * iwr;
         q2 += S.uh[c] * S.uh[c];
         un += S.uh[c] * S.n[c];
     }
     S.un = un;
-    S.Hh = (wL * T(HL) + wR * T(HR)) * iwr;
-    const T c2 = T(gm1) * (S.Hh - T(0.5) * q2);
+    S.Hh = prod2(wR, T(HR), wL, T(HL)) * iwr;
+    const T c2 = T(gm1) * fma(T(-0.5), q2, S.Hh);
     const T ic = rsq1<T>(c2);
     S.ch = c2 * ic;
     S.hq2 = T(0.5) * q2;
@@ -470,7 +513,7 @@ __device__ __forceinline__ void roe(const LD& ld, const SchemeK& sk, const FaceR
     if constexpr (DIM == 2) {
         S.t1[0] = -S.n[1];
         S.t1[1] = S.n[0];
-        S.ut1 = S.uh[0] * S.t1[0] + S.uh[1] * S.t1[1];
+        S.ut1 = prod2(S.uh[1], S.t1[1], S.uh[0], S.t1[0]);
         S.ut2 = T(0);
     } else {
         // a = argmin |n_k|, components within 1e-10 count as tied and the
@@ -485,15 +528,15 @@ __device__ __forceinline__ void roe(const LD& ld, const SchemeK& sk, const FaceR
         if (a == 0) { x0 = T(0); x1 = S.n[2]; x2 = -S.n[1]; }
         else if (a == 1) { x0 = -S.n[2]; x1 = T(0); x2 = S.n[0]; }
         else { x0 = S.n[1]; x1 = -S.n[0]; x2 = T(0); }
-        const T ix = rsq1<T>(x0 * x0 + x1 * x1 + x2 * x2);
+        const T ix = rsq1<T>(fma(x2, x2, prod2(x1, x1, x0, x0)));
         S.t1[0] = x0 * ix;
         S.t1[1] = x1 * ix;
         S.t1[2] = x2 * ix;
-        S.t2[0] = S.n[1] * S.t1[2] - S.n[2] * S.t1[1];
-        S.t2[1] = S.n[2] * S.t1[0] - S.n[0] * S.t1[2];
-        S.t2[2] = S.n[0] * S.t1[1] - S.n[1] * S.t1[0];
-        S.ut1 = S.uh[0] * S.t1[0] + S.uh[1] * S.t1[1] + S.uh[2] * S.t1[2];
-        S.ut2 = S.uh[0] * S.t2[0] + S.uh[1] * S.t2[1] + S.uh[2] * S.t2[2];
+        S.t2[0] = prod2(S.n[1], S.t1[2], -S.n[2], S.t1[1]);
+        S.t2[1] = prod2(S.n[2], S.t1[0], -S.n[0], S.t1[2]);
+        S.t2[2] = prod2(S.n[0], S.t1[1], -S.n[1], S.t1[0]);
+        S.ut1 = fma(S.uh[2], S.t1[2], prod2(S.uh[1], S.t1[1], S.uh[0], S.t1[0]));
+        S.ut2 = fma(S.uh[2], S.t2[2], prod2(S.uh[1], S.t2[1], S.uh[0], S.t2[0]));
     }
 }
 
@@ -501,14 +544,19 @@ __device__ __forceinline__ void roe(const LD& ld, const SchemeK& sk, const FaceR
 // phase C helper: reference-subtracted values and LF speeds at one node
 // ---------------------------------------------------------------------------
 
-// n.u and the sound speed of a node
-template <int DIM, typename T>
-__device__ __forceinline__ void node_speeds(const SchemeK& sk, const Eig<DIM, T>& S, const Prim<DIM>& P, T& un,
-                                            T& cs) {
+// n.u and the sound speed of a node of pressure p
+template <int DIM, typename T, bool CT>
+__device__ __forceinline__ void node_speeds(const SchemeK& sk, const Eig<DIM, T>& S, const Prim<DIM>& P, double p,
+                                            T& un, T& cs) {
     un = T(0);
 #pragma unroll
     for (int c = 0; c < DIM; ++c) un += S.n[c] * T(P.u[c]);
-    cs = T(sk.sg) * fmax(T(P.ct), T(0));
+    if constexpr (CT) {
+        cs = T(sk.sg) * fmax(T(P.ct), T(0));
+    } else {
+        const T c2 = T(sk.gamma * p) * rcp1<T>(T(P.rho));
+        cs = c2 > T(0) ? c2 * rsq1<T>(c2) : T(0);
+    }
 }
 
 template <int DIM, typename T>
@@ -532,18 +580,19 @@ __device__ __forceinline__ void node_diff(const LD& ld, int r, const SchemeK& sk
         U += P.u[c] * s[c];
         Us += R.us[c] * s[c];
     }
-    const double p = P.rho * P.ct * fabs(P.ct);
+    const double p = pressure(P, sk.gamma - 1.0);
     const double dp = p - R.ps;
-    const double m = P.rho * U;
-    N.dF[0] = m - R.Qs[0] * Us;
-#pragma unroll
-    for (int c = 0; c < DIM; ++c) N.dF[1 + c] = m * P.u[c] - R.Qs[1 + c] * Us + dp * s[c];
-    N.dF[E] = m * P.e + p * U - (R.Qs[E] + R.ps) * Us;
+    N.dF[0] = prod2(P.rho, U, -R.Qs[0], Us);
     N.dQ[0] = (P.rho - R.Qs[0]) * V;
 #pragma unroll
-    for (int c = 0; c < DIM; ++c) N.dQ[1 + c] = fma(P.rho, P.u[c], -R.Qs[1 + c]) * V;
-    N.dQ[E] = fma(P.rho, P.e, -R.Qs[E]) * V;
-    node_speeds<DIM, T>(sk, S, P, N.un, N.cs);
+    for (int c = 0; c < DIM; ++c) {
+        const double m = momentum(P, c);
+        N.dF[1 + c] = fma(dp, s[c], prod2(m, U, -R.Qs[1 + c], Us));
+        N.dQ[1 + c] = (m - R.Qs[1 + c]) * V;
+    }
+    N.dF[E] = prod2(P.E + p, U, -(R.Qs[E] + R.ps), Us);
+    N.dQ[E] = (P.E - R.Qs[E]) * V;
+    node_speeds<DIM, T, LD::CT>(sk, S, P, p, N.un, N.cs);
 }
 
 // l_s . w for the five (four in 2D) fields, using the structure of the Euler
@@ -564,12 +613,12 @@ __device__ __forceinline__ void project(const Eig<DIM, T>& S, const T (&w)[DIM +
         if constexpr (DIM == 3) t2w += S.t2[c] * w[1 + c];
     }
     const T phi = S.pB * (S.hq2 * w[0] - uw + w[E]);
-    const T psi = (nw - S.un * w[0]) * S.pI;
-    a[0] = phi - psi;
-    a[1] = w[0] - T(2) * phi;
+    const T nu = nw - S.un * w[0];  // psi = nu pI
+    a[0] = fma(-nu, S.pI, phi);
+    a[1] = fma(T(-2), phi, w[0]);
     a[2] = t1w - S.ut1 * w[0];
     if constexpr (DIM == 3) a[3] = t2w - S.ut2 * w[0];
-    a[E] = phi + psi;
+    a[E] = fma(nu, S.pI, phi);
 }
 
 // R h: back to conservative components
@@ -582,12 +631,12 @@ __device__ __forceinline__ void backproject(const Eig<DIM, T>& S, const T (&h)[D
     o[0] = hsum;
 #pragma unroll
     for (int c = 0; c < DIM; ++c) {
-        T m = S.uh[c] * hsum + S.ch * S.n[c] * hdif + S.t1[c] * h[2];
-        if constexpr (DIM == 3) m += S.t2[c] * h[3];
+        T m = fma(S.t1[c], h[2], prod2(S.ch * S.n[c], hdif, S.uh[c], hsum));
+        if constexpr (DIM == 3) m = fma(S.t2[c], h[3], m);
         o[1 + c] = m;
     }
-    T en = S.Hh * (h0 + hE) + S.ch * S.un * hdif + S.hq2 * h1 + S.ut1 * h[2];
-    if constexpr (DIM == 3) en += S.ut2 * h[3];
+    T en = fma(S.ut1, h[2], fma(S.hq2, h1, prod2(S.ch * S.un, hdif, S.Hh, h0 + hE)));
+    if constexpr (DIM == 3) en = fma(S.ut2, h[3], en);
     o[E] = en;
 }
 
@@ -735,8 +784,11 @@ __device__ __forceinline__ void face_flux_weno7(const LD& ld, const SchemeK& sk,
 // it as one term per face: central6(dF~) = central6(F~) - F(Q*).s6 with
 // s6 = central6(s).  With the add-back F(Q*).s_f the flux keeps
 // F(Q*).(s_f - s6), which vanishes for sixth-order metrics, whose
-// interpolation is central6 itself.  (The fifth difference takes Q - Q* node
-// by node: its weights would amplify the rounding of Q.)
+// interpolation is central6 itself; s_f - s6 is summed from the difference of
+// the weights, free of the rounding of two sums.  The pressure takes p - p*
+// node by node, and the whole p* s_f at the face: at low Mach numbers its
+// rounding would be the flux's largest.  (The fifth difference takes Q - Q*
+// node by node: its weights would amplify the rounding of Q.)
 
 template <int DIM, int Y, typename T, class LD>
 __device__ __forceinline__ void face_flux_lu5(const LD& ld, const SchemeK& sk,
@@ -748,7 +800,7 @@ __device__ __forceinline__ void face_flux_lu5(const LD& ld, const SchemeK& sk,
     face_ref<DIM, Y>(ld, sk, R);
     Eig<DIM, T> S;
     roe<DIM, T>(ld.after(R.Vf), sk, R, S);
-    double cen[NV], del[NV], s6[DIM];
+    double cen[NV], del[NV], s6[DIM];  // s6: s_f - central6(s)
 #pragma unroll
     for (int v = 0; v < NV; ++v) cen[v] = del[v] = 0.0;
 #pragma unroll
@@ -764,39 +816,45 @@ __device__ __forceinline__ void face_flux_lu5(const LD& ld, const SchemeK& sk,
         ln.metric(r, V, s);
 #pragma unroll
         for (int c = 0; c < DIM; ++c) U += P.u[c] * s[c];
-        const double wr = c6[r - 1] * P.rho, wm = wr * U, rr = P.ct * fabs(P.ct), wp = wr * rr;
+        const double w6 = c6[r - 1], wm = w6 * P.rho * U, p = pressure(P, sk.gamma - 1.0), wp = w6 * (p - R.ps);
         cen[0] += wm;
 #pragma unroll
         for (int c = 0; c < DIM; ++c) cen[1 + c] = fma(wm, P.u[c], fma(wp, s[c], cen[1 + c]));
-        cen[E] = fma(wm, P.e + rr, cen[E]);
+        cen[E] = fma(w6 * U, P.E + p, cen[E]);
         const double wV = d5[r - 1] * V;
         del[0] = fma(wV, P.rho - R.Qs[0], del[0]);
 #pragma unroll
         for (int c = 0; c < DIM; ++c) del[1 + c] = fma(wV, fma(P.rho, P.u[c], -R.Qs[1 + c]), del[1 + c]);
-        del[E] = fma(wV, fma(P.rho, P.e, -R.Qs[E]), del[E]);
+        del[E] = fma(wV, P.E - R.Qs[E], del[E]);
         if constexpr (Y != 6) {
 #pragma unroll
-            for (int c = 0; c < DIM; ++c) s6[c] += c6[r - 1] * s[c];
+            for (int c = 0; c < DIM; ++c) s6[c] += (iw<Y>(r) - w6) * s[c];
         }
         chain = del[0];
         T un, cs;
-        node_speeds<DIM, T>(sk, S, P, un, cs);
+        node_speeds<DIM, T, LD::CT>(sk, S, P, p, un, cs);
         mxm = fmax(mxm, fabs(un - cs));
         mx0 = fmax(mx0, fabs(un));
         mxp = fmax(mxp, fabs(un + cs));
     }
-    if constexpr (Y != 6) {
+    if constexpr (Y == 8) {
+        double V, s0[DIM], s7[DIM];
+        ld.after(chain).metric(0, V, s0);
+        ld.after(chain).metric(7, V, s7);
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) s6[c] += iw<8>(0) * (s0[c] + s7[c]);
+    }
+    if constexpr (Y != 6) {  // F(Q*).(s_f - s6) but for the pressure
         double U = 0.0;
 #pragma unroll
-        for (int c = 0; c < DIM; ++c) {
-            s6[c] = R.sf[c] - s6[c];
-            U += R.us[c] * s6[c];
-        }
+        for (int c = 0; c < DIM; ++c) U += R.us[c] * s6[c];
         cen[0] = fma(R.Qs[0], U, cen[0]);
 #pragma unroll
-        for (int c = 0; c < DIM; ++c) cen[1 + c] = fma(R.Qs[1 + c], U, fma(R.ps, s6[c], cen[1 + c]));
+        for (int c = 0; c < DIM; ++c) cen[1 + c] = fma(R.Qs[1 + c], U, cen[1 + c]);
         cen[E] = fma(R.Qs[E] + R.ps, U, cen[E]);
     }
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) cen[1 + c] = fma(R.ps, R.sf[c], cen[1 + c]);
     T w[NV], pa[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) w[v] = T(del[v]);

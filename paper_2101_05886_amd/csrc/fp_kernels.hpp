@@ -183,6 +183,7 @@ __device__ __forceinline__ void epi_store(const EpiK& ep, long vol, long off, co
 // directly: fp_metrics fills their ghost layers.
 template <int DIM, int DIR>
 struct LineLoader {
+    static constexpr bool CT = true;
     const double* __restrict__ met;
     const double* q;
     long vol;       // elements per variable
@@ -243,8 +244,8 @@ struct LineLoader {
     }
 };
 
-// Slot access of a loader to nodes staged in LDS as primitives: `at(r, v)` is
-// value v of slot r in the order rho, u, e, 1/J, s, ct.
+// Slot access of a loader to nodes staged in LDS: `at(r, v)` is
+// value v of slot r in the order rho, u, E, 1/J, s, ct.
 template <int DIM, class LD>
 struct StagedNodes {
     __device__ __forceinline__ const LD& self() const { return static_cast<const LD&>(*this); }
@@ -252,8 +253,8 @@ struct StagedNodes {
         P.rho = self().at(r, 0);
 #pragma unroll
         for (int c = 0; c < DIM; ++c) P.u[c] = self().at(r, 1 + c);
-        P.e = self().at(r, DIM + 1);
-        P.ct = self().at(r, 2 * DIM + 3);
+        P.E = self().at(r, DIM + 1);
+        if constexpr (LD::CT) P.ct = self().at(r, 2 * DIM + 3);
     }
     __device__ __forceinline__ void metric(int r, double& V, double (&s)[DIM]) const {
         V = self().at(r, DIM + 2);
@@ -270,7 +271,8 @@ struct StagedNodes {
         for (int c = 0; c < DIM; ++c) sf[c] += w * s[c];
         Qt[0] += wVr;
 #pragma unroll
-        for (int c = 0; c <= DIM; ++c) Qt[1 + c] = fma(wVr, self().at(r, 1 + c), Qt[1 + c]);
+        for (int c = 0; c < DIM; ++c) Qt[1 + c] = fma(wVr, self().at(r, 1 + c), Qt[1 + c]);
+        Qt[DIM + 1] = fma(wV, self().at(r, DIM + 1), Qt[DIM + 1]);
     }
 };
 
@@ -340,7 +342,7 @@ __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane
 template <int DIM, int NE_>
 struct XLds {
     static constexpr int NE = NE_;          // staged entries per buffer
-    static constexpr int NS = 2 * DIM + 3;  // q, 1/J, s_xi; the state as primitives once converted
+    static constexpr int NS = 2 * DIM + 3;  // q, 1/J, s_xi; the momentum as velocity once converted
     alignas(16) double b[2][NS][NE];        // double buffer: current item, next item
     double ct[NE];                          // the thermal speed of the current item's nodes
 };
@@ -537,8 +539,8 @@ __device__ __forceinline__ void x_stage(const GeoK& G, const double* __restrict_
     }
 }
 
-// Primitives of an item's entries in place of their conserved state: each
-// entry serves the six to eight faces around it.
+// Velocity and thermal speed of an item's entries, the former in place of the
+// momentum: each entry serves the six to eight faces around it.
 template <int DIM, int NE>
 __device__ __forceinline__ void x_convert(unsigned count, double gm1, double (*buf)[NE], double* ct) {
     constexpr int NV = DIM + 2;
@@ -550,7 +552,6 @@ __device__ __forceinline__ void x_convert(unsigned count, double gm1, double (*b
         to_prim<DIM>(q, gm1, P);
 #pragma unroll
         for (int c = 0; c < DIM; ++c) buf[1 + c][e] = P.u[c];
-        buf[NV - 1][e] = P.e;
         ct[e] = P.ct;
     }
     // other lanes of the wave read these entries (LDS operations of a wave
@@ -562,6 +563,7 @@ __device__ __forceinline__ void x_convert(unsigned count, double gm1, double (*b
 // Stencil reads of one lane's xi face from the wave's staged entries.
 template <int DIM, int NE>
 struct XLoader : StagedNodes<DIM, XLoader<DIM, NE>> {
+    static constexpr bool CT = true;
     const double (*buf)[NE];
     const double* ct;
     unsigned ea;  // byte offset of entry e(F) in a variable row
@@ -686,9 +688,9 @@ constexpr int wide_stencil(int recon, int Y) { return (recon == 2 || Y == 8) ? 1
 template <int DIM, int WIDE>
 struct WgLds {
     static constexpr int NV = DIM + 2;
-    // values per node: the state as primitives, 1/J, s_DIR and, where the LDS
-    // has room beside two resident workgroups, the thermal speed; else that
-    // takes the place of E/rho, which the reads then rebuild from it
+    // values per node: density, velocity, energy, 1/J, s_DIR and, where the
+    // LDS has room beside two resident workgroups, the thermal speed; else the
+    // faces take the sound speed from the pressure
     static constexpr bool CT = !(WIDE && DIM == 3);
     static constexpr int NS = 2 * DIM + 3 + (CT ? 1 : 0);
     static constexpr int LO = WIDE ? 3 : 2;  // nodes below node i a face i+1/2 reads
@@ -705,10 +707,10 @@ struct WgLds {
 template <int DIM, int WIDE>
 struct LdsLoader : StagedNodes<DIM, LdsLoader<DIM, WIDE>> {
     using W = WgLds<DIM, WIDE>;
+    static constexpr bool CT = W::CT;
     const W* L;
     unsigned la;  // byte offset of this lane in a ring row
     int b0;       // ring row of slot 0, in [0, RING)
-    double igm1;  // 1 / (gamma - 1)
 
     __device__ __forceinline__ LdsLoader after(double dep) const {
         LdsLoader c = *this;
@@ -716,28 +718,15 @@ struct LdsLoader : StagedNodes<DIM, LdsLoader<DIM, WIDE>> {
         return c;
     }
 
-    __device__ __forceinline__ double raw(int r, int v) const {
+    __device__ __forceinline__ double at(int r, int v) const {
         int idx = b0 + r;
         idx = idx >= W::RING ? idx - W::RING : idx;
         return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(&L->ring[idx][0][0]) + la + v * 512);
     }
-    __device__ __forceinline__ double at(int r, int v) const {
-        if constexpr (!W::CT) {
-            if (v == 2 * DIM + 3) return raw(r, DIM + 1);
-            if (v == DIM + 1) {
-                const double ct = raw(r, DIM + 1);
-                double k2 = 0.0;
-#pragma unroll
-                for (int c = 0; c < DIM; ++c) k2 = fma(raw(r, 1 + c), raw(r, 1 + c), k2);
-                return fma(0.5, k2, ct * fabs(ct) * igm1);
-            }
-        }
-        return raw(r, v);
-    }
 };
 
-// Primitives of one ring row in place of its conserved state (a wave, one
-// line per lane; the row's DMA must have landed).
+// Velocity and thermal speed of one ring row, the former in place of the
+// momentum (a wave, one line per lane; the row's DMA must have landed).
 template <int DIM, int WIDE>
 __device__ __forceinline__ void wg_convert(WgLds<DIM, WIDE>& L, int slot, double gm1) {
     constexpr int NV = DIM + 2;
@@ -749,12 +738,7 @@ __device__ __forceinline__ void wg_convert(WgLds<DIM, WIDE>& L, int slot, double
     to_prim<DIM>(q, gm1, P);
 #pragma unroll
     for (int c = 0; c < DIM; ++c) L.ring[slot][1 + c][lane] = P.u[c];
-    if constexpr (WgLds<DIM, WIDE>::CT) {
-        L.ring[slot][NV - 1][lane] = P.e;
-        L.ring[slot][2 * DIM + 3][lane] = P.ct;
-    } else {
-        L.ring[slot][NV - 1][lane] = P.ct;
-    }
+    if constexpr (WgLds<DIM, WIDE>::CT) L.ring[slot][2 * DIM + 3][lane] = P.ct;
 }
 
 // eta / zeta sweeps: a workgroup of four waves takes a block of 64 grid lines
@@ -764,14 +748,17 @@ __device__ __forceinline__ void wg_convert(WgLds<DIM, WIDE>& L, int slot, double
 // per wave per iteration, prefetched one iteration ahead.  Per iteration
 // wave w evaluates the face f+1/2, f = k0 - 1 + 4 it + w, on its 64 lines
 // from the ring, the fluxes go to LDS and wave w forms node f's difference
-// F'_{f+1/2} - F'_{f-1/2}.  Each wave turns its row into primitives once its
-// DMA has landed, before the barrier that publishes it.  Bound by vector
-// issue.  With the primitives formed per node instead of per face, and no
-// wait for stores between the barriers, an RK3 step of a 256^3 block took
-// 9.25 ms against 9.85 in FP64 WENO5 (three sweeps per stage), 8.08 against
-// 8.29 FP32-mixed, and one of 128^3 with LU5 0.77 against 0.87.  Every thread
-// of the workgroup runs the same iterations and barriers.  A caller that reuses `L` for another item must
-// synchronise the workgroup first.
+// F'_{f+1/2} - F'_{f-1/2}.  Each wave forms its row's velocities and thermal
+// speeds once its DMA has landed, before the barrier that publishes it.  Bound
+// by vector issue.  With the quotients and roots per node instead of per face,
+// no wait for stores between the barriers and the xi sweep's and workgroup
+// orders above, an RK3 step of a 256^3 block takes 9.05 ms against 9.71 in
+// FP64 WENO5 (three sweeps per stage), 7.96 against 8.21 FP32-mixed, and two
+// of 128^3 with LU5 1.53 against 1.73.  (Without the momentum and pressure
+// products that keep the residual's rounding down: 8.86, 7.75 and 1.46.)
+// Every thread of the workgroup runs the same iterations and barriers.  A
+// caller that reuses `L` for another item must synchronise the workgroup
+// first.
 // (the batched sweep has something to do when the item's first rows have
 // arrived)
 struct Nothing {
@@ -858,7 +845,6 @@ __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
             ld.L = &L;
             ld.la = (unsigned)lane * 8u;
             ld.b0 = (f - 3 - tb + W::RING) % W::RING;
-            ld.igm1 = sk.igm1;
             face_flux<DIM, RECON, Y, char_t<PREC>>(ld, sk, F);
         }
 #pragma unroll
@@ -964,7 +950,7 @@ struct RowLds {
     static constexpr int NC = 64;  // columns: x = i0 - 4 .. i0 + 59
     static constexpr int LO = WIDE ? 3 : 2, HI = WIDE ? 4 : 3;
     static constexpr int ROWS = 2 + LO + HI;  // nodes k - 1 - LO .. k + HI
-    static constexpr int NS = 8;              // rho, u, v, E/rho, 1/J, s_eta, thermal speed
+    static constexpr int NS = 8;              // rho, u, v, E, 1/J, s_eta, thermal speed
     double row[ROWS][NS][NC];
     double sx[2][NC];        // s_xi of row k
     double flux[2][4][NC];   // the two eta faces
@@ -974,6 +960,7 @@ struct RowLds {
 // row b0 + r, or column r of row k.
 template <int WIDE>
 struct RowLoader : StagedNodes<2, RowLoader<WIDE>> {
+    static constexpr bool CT = true;
     using W = RowLds<WIDE>;
     const W* L;
     unsigned la;  // byte offset of this lane's column
@@ -1080,7 +1067,6 @@ __global__ __launch_bounds__(256) FP_SWEEP_ATTR void k_row_2d(GeoK G, SchemeK sk
         to_prim<2>(q, gm1, P);
         L.row[r][1][lane] = P.u[0];
         L.row[r][2][lane] = P.u[1];
-        L.row[r][3][lane] = P.e;
         L.row[r][7][lane] = P.ct;
     }
     lds_barrier();
