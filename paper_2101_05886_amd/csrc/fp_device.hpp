@@ -796,6 +796,9 @@ __device__ __forceinline__ void face_flux_lu5(const LD& ld, const SchemeK& sk,
     constexpr int NV = DIM + 2, E = NV - 1;
     constexpr double c6[6] = {1.0 / 60, -8.0 / 60, 37.0 / 60, 37.0 / 60, -8.0 / 60, 1.0 / 60};
     constexpr double d5[6] = {1.0, -5.0, 10.0, -10.0, 5.0, -1.0};
+    // weights of s_f - s6 on slots 1..6
+    constexpr double df[6] = {iw<Y>(1) - c6[0], iw<Y>(2) - c6[1], iw<Y>(3) - c6[2],
+                              iw<Y>(4) - c6[3], iw<Y>(5) - c6[4], iw<Y>(6) - c6[5]};
     FaceRef<DIM> R;
     face_ref<DIM, Y>(ld, sk, R);
     Eig<DIM, T> S;
@@ -807,6 +810,15 @@ __device__ __forceinline__ void face_flux_lu5(const LD& ld, const SchemeK& sk,
     for (int c = 0; c < DIM; ++c) s6[c] = 0.0;
     T mxm = T(0), mx0 = T(0), mxp = T(0);
     double chain = double(S.pI);
+    if constexpr (Y == 8) {  // the outermost nodes
+        const LD ln = ld.after(chain);
+        double V, s0[DIM], s7[DIM];
+        ln.metric(0, V, s0);
+        ln.metric(7, V, s7);
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) s6[c] = iw<8>(0) * (s0[c] + s7[c]);
+        chain = s6[0];
+    }
 #pragma unroll
     for (int r = 1; r <= 6; ++r) {
         const LD ln = ld.after(chain);
@@ -828,7 +840,7 @@ __device__ __forceinline__ void face_flux_lu5(const LD& ld, const SchemeK& sk,
         del[E] = fma(wV, P.E - R.Qs[E], del[E]);
         if constexpr (Y != 6) {
 #pragma unroll
-            for (int c = 0; c < DIM; ++c) s6[c] += (iw<Y>(r) - w6) * s[c];
+            for (int c = 0; c < DIM; ++c) s6[c] += df[r - 1] * s[c];
         }
         chain = del[0];
         T un, cs;
@@ -836,13 +848,6 @@ __device__ __forceinline__ void face_flux_lu5(const LD& ld, const SchemeK& sk,
         mxm = fmax(mxm, fabs(un - cs));
         mx0 = fmax(mx0, fabs(un));
         mxp = fmax(mxp, fabs(un + cs));
-    }
-    if constexpr (Y == 8) {
-        double V, s0[DIM], s7[DIM];
-        ld.after(chain).metric(0, V, s0);
-        ld.after(chain).metric(7, V, s7);
-#pragma unroll
-        for (int c = 0; c < DIM; ++c) s6[c] += iw<8>(0) * (s0[c] + s7[c]);
     }
     if constexpr (Y != 6) {  // F(Q*).(s_f - s6) but for the pressure
         double U = 0.0;
