@@ -701,6 +701,8 @@ struct WgLds {
     double flux[4][NV][64];  // the four faces of the current iteration
     double carry[NV][64];    // the last face of the previous iteration
 };
+static_assert(2 * sizeof(WgLds<3, 0>) <= 160 * 1024 && 2 * sizeof(WgLds<3, 1>) <= 160 * 1024,
+              "two workgroups per CU");
 
 // Stencil reads of face i+1/2 from the LDS ring: slot r (node i-3+r) is ring
 // row (b0 + r) mod RING.
@@ -1434,13 +1436,18 @@ __global__ __launch_bounds__(256) FP_XSWEEP_ATTR(PREC, RECON, Y) void kb_sweep_x
 // for it (24 serving blocks, few items per workgroup, handed out: 4.84 ->
 // 4.93 ms for five steps).  The xi sweep's items are too small to be
 // handed out: the same serving blocks took 9.1 ms.
+// Two workgroups per CU, but one for FP64 WENO7 in 3D, which spills some 45
+// registers at two and none with the registers of one: 16 body blocks 26.7 ms
+// per step against 36.2, 12 serving blocks 2.02 against 2.46.  The other wide
+// FP64 stencils spill eight at most: WENO5 with eighth-order metrics 20.6 ms
+// with one workgroup, 19.4 with two, WENOCU6 27.0 and 26.0, LU5 15.1 and 13.7.
+#define FP_BWAVES(DIM, RECON, PREC) ((DIM) == 3 && (RECON) == 2 && (PREC) == 0 ? 1 : 2)
 template <int DIM, int DIR, int RECON, int Y, int PREC>
-__global__ __launch_bounds__(256) FP_SWEEP_ATTR void kb_sweep_wg(const int* __restrict__ t_nblk,
-                                                                 const long* __restrict__ t_start,
-                                                                 const BBlock* __restrict__ t_blk, int cap,
-                                                                 SchemeK sk, int stage, unsigned* next) {
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(FP_BWAVES(DIM, RECON, PREC), FP_BWAVES(DIM, RECON, PREC))))
+void kb_sweep_wg(const int* __restrict__ t_nblk, const long* __restrict__ t_start,
+                 const BBlock* __restrict__ t_blk, int cap, SchemeK sk, int stage, unsigned* next) {
     __shared__ WgLds<DIM, wide_stencil(RECON, Y)> lds;
-    __shared__ unsigned taken[2];
     constexpr int KIND = DIR == 1 ? BK_ETA : BK_ZETA;
     constexpr int MODE = DIR == DIM - 1 ? EPI_LAST_RK : EPI_MID;
     const int nblk = *t_nblk;
@@ -1450,8 +1457,7 @@ __global__ __launch_bounds__(256) FP_SWEEP_ATTR void kb_sweep_wg(const int* __re
     if (blockIdx.x >= total) return;
     const bool handed = total > 6 * gridDim.x;
     int b = find_block(st, nblk, blockIdx.x);
-    int cur = 0;
-    for (unsigned item = blockIdx.x; item < total; cur ^= 1) {
+    for (unsigned item = blockIdx.x; item < total;) {
         b = advance_block(st, nblk, b, item);
         const BBlock& B = t_blk[ord[b]];
         const EpiK ep = stage_epi(B, stage, MODE, DIM);
@@ -1459,19 +1465,29 @@ __global__ __launch_bounds__(256) FP_SWEEP_ATTR void kb_sweep_wg(const int* __re
         const unsigned lblocks = (unsigned)(((long)B.G.n[0] * B.G.n[OTH] + 63) / 64);
         const unsigned in = item - (unsigned)st[b];
         const int k0 = (int)(in / lblocks) * B.S[DIR];
-        unsigned c = 0;
+        unsigned c = 0, taken = 0;
         if (handed && threadIdx.x == 0)
             c = __hip_atomic_fetch_add(next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         sweep_wg_item<DIM, DIR, RECON, Y, PREC>(B.G, sk, B.met, stage_in(B, stage), ep, (int)(in % lblocks), k0,
                                                 min(k0 + B.S[DIR], B.G.n[DIR]), lds, [&] {
-                                                    if (threadIdx.x != 0) return;
-                                                    taken[cur] = handed ? c + gridDim.x : item + gridDim.x;
-                                                    if (handed && c + 1 == total)
+                                                    taken = (unsigned)__builtin_amdgcn_readfirstlane((int)c);
+                                                    if (handed && threadIdx.x == 0 && c + 1 == total)
                                                         __hip_atomic_store(next, 0u, __ATOMIC_RELAXED,
                                                                            __HIP_MEMORY_SCOPE_AGENT);
                                                 });
-        __syncthreads();  // the next item rewrites the LDS ring
-        item = (unsigned)__builtin_amdgcn_readfirstlane((int)taken[cur]);
+        if (handed) {
+            // the answer, in a scalar register of the first wave, goes round
+            // through a flux that has been read and is written again only
+            // after the next item's first barrier: a word of LDS more would
+            // leave wide 3D stencils one workgroup per CU
+            unsigned* word = reinterpret_cast<unsigned*>(&lds.flux[0][0][0]);
+            if (threadIdx.x == 0) *word = taken;
+            __syncthreads();
+            item = (unsigned)__builtin_amdgcn_readfirstlane((int)*word) + gridDim.x;
+        } else {
+            __syncthreads();  // the next item rewrites the LDS ring
+            item += gridDim.x;
+        }
     }
 }
 
