@@ -60,3 +60,9 @@ def test_two_workgroups_of_the_sweeps_fit_a_cu(kernels):
                 assert k[".private_segment_fixed_size"] == 0, args
             else:
                 assert k[".vgpr_count"] <= 256, (name, args)
+
+
+def test_metrics_2d_registers(kernels):
+    # a lane per node: latency is hidden by other waves, four per SIMD or more
+    for args, k in kernels["k_metrics2"]:
+        assert k[".vgpr_count"] <= 128 and k[".private_segment_fixed_size"] == 0, args
