@@ -53,8 +53,8 @@ constexpr int kGlfSetStride = 3 * kGlfDirStride;
 //             out = u (first stage) or a qn + b u (TVD RK3 stages 2, 3)
 enum { EPI_FIRST = 0, EPI_MID = 1, EPI_LAST_RES = 2, EPI_LAST_RK = 3 };
 
-// The eta / zeta sweeps, which apply the final epilogues, take 1/J from the
-// stencil rows they staged.
+// The kernels that apply the final epilogues take 1/J and, qin being the array
+// they read, its density and energy from the stencil rows they staged.
 struct EpiK {
     int mode;
     int stage0;
@@ -113,8 +113,9 @@ struct EpiPre {
     double R[NV], qin[NV], qn[NV], V;
 };
 
-// (the final epilogues' callers supply 1/J from the rows they staged; they
-// may take the stage input later, with epi_load_qin)
+// (the final epilogues' callers supply 1/J and the stage input's density and
+// energy from the rows they staged, which hold its momentum as velocity; they
+// may take the momentum later, with epi_load_qin)
 // (buffer loads and stores: one 32-bit byte offset per lane serves every
 // variable array, whose base goes into the wave-uniform resource)
 template <int NV>
@@ -122,7 +123,7 @@ __device__ __forceinline__ void epi_load_qin(const EpiK& ep, long vol, long off,
     if (ep.mode != EPI_LAST_RK) return;
     const double* qin = rebase(ep.qin);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) p.qin[v] = ldb(qin + v * vol, vol, (unsigned)off * 8u);
+    for (int v = 1; v < NV - 1; ++v) p.qin[v] = ldb(qin + v * vol, vol, (unsigned)off * 8u);
 }
 template <int NV>
 __device__ __forceinline__ void epi_load(const EpiK& ep, long vol, long off, EpiPre<NV>& p, bool with_qin) {
@@ -801,9 +802,8 @@ __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
     const int tb = k0 - 1 - W::LO;            // node index of ring row 0
     const int tmax = k1 - 1 + W::HI;          // last row any needed face reads
     const double gm1 = sk.gamma - 1.0;
-    // the stage input of the final epilogue: FP32 loads it with the other
-    // operands, FP64, which would spill, after the face (this workgroup's DMA
-    // read those lines an iteration or two before: L2 hits)
+    // the stage input's momentum for the final epilogue: FP32 loads it with
+    // the other operands, FP64, which would spill, after the face
     constexpr bool late_qin = sizeof(char_t<PREC>) == 8;
     auto load_row = [&](int t) {
         if (t > tmax) return;
@@ -834,7 +834,7 @@ __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
         const int f = k0 - 1 + 4 * it + w;
         if (it + 1 < iters) load_row(tb + W::WIN + 4 * it + w);  // a row of the next iteration
         // this wave's node f: its epilogue operands load while the face is
-        // computed; 1/J is in its ring row already
+        // computed; 1/J, density and energy are in its ring row already
         const bool mine = lane_ok && f >= k0 && f < k1;
         const long noff = lb + (long)f * G.sd[DIR];
         EpiPre<NV> pre;
@@ -862,10 +862,15 @@ __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
         // overwrite them.  Only those reads lie between the two; the epilogue
         // and its stores follow, beside the next face.
         lds_barrier();
-        double prev[NV], V = 0.0;
+        double prev[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) prev[v] = (w > 0 ? &L.flux[w - 1][0][0] : &L.carry[0][0])[v * 64 + lane];
-        if (ep.mode >= EPI_LAST_RES) V = L.ring[(f - tb) % W::RING][NV][lane];
+        if (ep.mode >= EPI_LAST_RES) {
+            const double (*row)[64] = L.ring[(f - tb) % W::RING];
+            pre.V = row[NV][lane];
+            pre.qin[0] = row[0][lane];
+            pre.qin[NV - 1] = row[NV - 1][lane];
+        }
         lds_barrier();
         if (w == 3) {  // the next iteration's first face needs this one's last flux
 #pragma unroll
@@ -875,7 +880,6 @@ __device__ __forceinline__ void sweep_wg_item(const GeoK& G, const SchemeK& sk,
             double d[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v) d[v] = F[v] - prev[v];
-            pre.V = V;
             epi_store<NV>(ep, G.vol, noff, pre, d);
         }
     }
@@ -1102,6 +1106,8 @@ __global__ __launch_bounds__(256) FP_SWEEP_ATTR void k_row_2d(GeoK G, SchemeK sk
             pre.R[v] = ACC ? pre.R[v] - d[v] : -d[v];
         }
         pre.V = L.row[W::LO + 1][4][lane + 3];
+        pre.qin[0] = L.row[W::LO + 1][0][lane + 3];
+        pre.qin[NV - 1] = L.row[W::LO + 1][NV - 1][lane + 3];
         epi_store<NV>(ep, vol, noff, pre, dy);
     }
 }
