@@ -125,7 +125,7 @@ hipError_t run_stage(const SweepArgs& a, hipStream_t s) {
     }
     if constexpr (DIM == 2) {
         // an instrumented step times the sweeps apart (bitwise the same)
-        if (!a.probe && row_2d_fits(a.G.n, R)) {
+        if (!a.probe && row_2d_fits(a.G.n)) {
             launch_row<Y>(a, s);
             return hipGetLastError();
         }

@@ -1112,16 +1112,13 @@ __global__ __launch_bounds__(256) FP_SWEEP_ATTR void k_row_2d(GeoK G, SchemeK sk
     }
 }
 
-// Workgroups of the kernel above, and whether it takes the block: one round of
-// the two that a CU holds, and half of a second for LU5, whose stages are the
-// shortest beside their launches.  us per stage in solves, against the two
-// sweeps: WENO5 FP64 110^2 (220 workgroups) 7.5 and 14.2, 168^2 (504) 11.0 and
-// 13.8, 56x540 14.2 and 14.1, 224^2 (896) 17.0 and 15.9; WENO7 FP64 504 13.5
-// and 16.2, 520 17.4 and 16.4; FP32-mixed WENOCU6 504 11.4 and 15.7, 540 16.1
-// and 16.0; LU5 504 9.0 and 12.0, 680 11.1 and 11.9, 800 13.3 and 13.4, 1000
-// 13.5 and 13.3.
+// Workgroups of the kernel above, and whether it takes the block: two rounds
+// of the two that a CU holds.  WENO5 FP64, us per stage, against the two
+// sweeps: 110^2 (220 workgroups) 7.5 and 14.2, 160^2 (480) 10.2 and 14.6,
+// 224^2 (896) 15.8 and 17.3, 30x1000 (1000) 16.2 and 17.0, 256^2 (1280) 19.1
+// and 19.3, 300^2 (1800) 26.9 and 20.3.
 inline long row_2d_blocks(const int n[3]) { return (long)((n[0] + kRowNodes - 1) / kRowNodes) * n[1]; }
-inline bool row_2d_fits(const int n[3], int recon) { return row_2d_blocks(n) <= (recon == 1 ? 768 : 512); }
+inline bool row_2d_fits(const int n[3]) { return row_2d_blocks(n) <= 1024; }
 
 // ---------------------------------------------------------------------------
 // global Lax-Friedrichs speeds
