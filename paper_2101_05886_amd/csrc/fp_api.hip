@@ -200,9 +200,14 @@ SchemeK make_sk(const fp_scheme* s) {
 // (below, launches last as long as one chain of load, face and store) to
 // `longest`: workgroups that march far drift apart and lose the cache lines
 // they share with their neighbours, which LU5, nearest to the HBM bound,
-// feels first.  RK3 step, uniform and balanced: 145x113x97 WENO5 FP64 937
-// and 904 us, 160^3 2,328 and 2,276, 180x120x150 LU5 1,190 and 1,165; above
-// the limit 200^3 LU5 2,835 and 3,112, WENO5 mixed 3,855 and 3,903.  S = 3,
+// feels first.  RK3 step, uniform and balanced, 145x113x97, 160^3 and
+// 180x120x150: WENO5 FP64 1,015 and 975, 2,412 and 2,381, 1,901 and 1,872 us;
+// FP32-mixed WENO7 1,167 and 1,122, 2,765 and 2,733, 2,237 and 2,144; LU5 655
+// and 633, 1,583 both, 1,242 and 1,228; WENOCU6 FP64 1,365 and 1,345, 3,300 and
+// 3,297, 2,609 and 2,593; FP64 WENO7, which spills 55 registers with the loop
+// over pieces and 36 without, 1,794 and 1,854, 4,526 and 4,639, 3,553 and
+// 3,516: even over sizes.  Above the limit 200^3 LU5 2,835 and 3,112, WENO5
+// mixed 3,855 and 3,903.  S = 3,
 // one iteration, is the shortest segment, and the best for blocks too small to
 // fill the chip (a 45x33x29 residual: 30.2 us with S = 4, two iterations, 24.0
 // with 3).

@@ -1113,10 +1113,14 @@ __global__ __launch_bounds__(256) FP_SWEEP_ATTR void k_row_2d(GeoK G, SchemeK sk
 }
 
 // Workgroups of the kernel above, and whether it takes the block: two rounds
-// of the two that a CU holds.  WENO5 FP64, us per stage, against the two
-// sweeps: 110^2 (220 workgroups) 7.5 and 14.2, 160^2 (480) 10.2 and 14.6,
-// 224^2 (896) 15.8 and 17.3, 30x1000 (1000) 16.2 and 17.0, 256^2 (1280) 19.1
-// and 19.3, 300^2 (1800) 26.9 and 20.3.
+// of the two that a CU holds.  us per stage against the two sweeps: WENO5 FP64
+// in a residual call 170^2 (680 workgroups) 16.1 and 21.9, 30x1000 (1000) 18.7
+// and 22.9; in an RK3 step 13.8 and 14.5, 16.5 and 16.9; in a captured step,
+// whose launches cost least, 168^2 (504) 11.0 and 13.8, then 13.8 and 13.7,
+// 17.0 and 16.1, and beyond the line 300^2 (1800) 28.8 and 18.0.
+// WENO7 in a residual call 680 workgroups 19.0 and 21.5, 1000 22.9 and 24.0,
+// captured 17.5 and 16.2, 21.6 and 19.5; LU5 captured 11.1 and 11.9, 13.5 and
+// 13.3.
 inline long row_2d_blocks(const int n[3]) { return (long)((n[0] + kRowNodes - 1) / kRowNodes) * n[1]; }
 inline bool row_2d_fits(const int n[3]) { return row_2d_blocks(n) <= 1024; }
 
