@@ -2,6 +2,8 @@
 // (precision, reconstruction) pair, selected at compile time by FP_INST_PREC
 // (0 = FP64, 1 = mixed FP32) and FP_INST_RECON (0 = WENO5-JS, 1 = linear
 // upwind, 2 = WENO7-JS, 3 = WENOCU6).  The build compiles this file once per pair, in parallel.
+#include <algorithm>
+
 #include "fp_kernels.hpp"
 
 #if !defined(FP_INST_PREC) || !defined(FP_INST_RECON)
@@ -84,11 +86,12 @@ template <int DIM, int Y, bool ACC>
 void launch_x_mode(const SweepArgs& a, const EpiK& ep, hipStream_t s) {
     static const int res = resident(&k_sweep_x<DIM, R, Y, P, ACC>);
     const long items = sweep_x_items(a.G.n, x_entries(P, R, Y));
-    const long wgs = (items + 3) / 4;
+    const unsigned wgs = (unsigned)std::min((items + 3) / 4, (long)res);
     GeoK G = a.G;
     G.xw = x_window(G.n[0], x_entries(P, R, Y));
-    hipLaunchKernelGGL((k_sweep_x<DIM, R, Y, P, ACC>), dim3((unsigned)(wgs < res ? wgs : res)), dim3(256), 0,
-                       s, G, a.sk, a.met, a.qs, ep);
+    const XPos step = x_pos(G, (wgs % 8 ? wgs * 4 : wgs / 2) * ((unsigned)G.xw - 1));  // waves of the grid or of an XCD
+    hipLaunchKernelGGL((k_sweep_x<DIM, R, Y, P, ACC>), dim3(wgs), dim3(256), 0, s, G, a.sk, a.met, a.qs, ep, step,
+                       (unsigned)items);
 }
 
 // the xi sweep writes the accumulator (FIRST), or adds to it after the

@@ -389,7 +389,7 @@ __device__ __forceinline__ void line_step(unsigned a1, unsigned a2, unsigned dL,
 struct XPos {
     unsigned F0, f0, a1, a2;
 };
-__device__ __forceinline__ XPos x_pos(const GeoK& G, unsigned F0) {
+__device__ __host__ __forceinline__ XPos x_pos(const GeoK& G, unsigned F0) {
     const unsigned nf = (unsigned)G.n[0] + 1, n1 = (unsigned)G.n[1];
     XPos p;
     const unsigned L0 = F0 / nf;
@@ -641,25 +641,31 @@ __device__ __forceinline__ void x_compute(const GeoK& G, const SchemeK& sk, cons
     }
 }
 
-// Persistent xi sweep of one block: wave w of the grid takes items w,
-// w + (waves of the grid), ..., staging the next item while it computes
-// (ACC: the epilogue is MID, not FIRST; those kernels run at two waves per
-// SIMD, the accumulator's registers do not fit three).
+// Persistent xi sweep of one block.  Where the grid is whole (a multiple of 8)
+// each XCD takes an eighth of the items, contiguous, and its waves go through
+// it side by side, so that the last items, less than one per wave, are spread
+// over all XCDs; in a smaller grid every wave has one item, in XCD-contiguous
+// order.  FP64 WENO5 96x80x70, 4.2 items per wave: 40.8 us, 45.4 with the last
+// items on the first XCDs, 42.6 with neighbouring items on different XCDs;
+// WENOCU6 80x64x60 33.0, 40.4 and 37.3; 256^3 the same.  A wave stages its next
+// item, `step` on, while it computes (ACC: the epilogue is MID, not
+// FIRST; those kernels run at two waves per SIMD, the accumulator's registers
+// do not fit three).
 #define FP_XWAVES_ACC(PREC, RECON, Y, ACC) ((ACC) ? 2 : FP_XWAVES(PREC, RECON, Y))
 template <int DIM, int RECON, int Y, int PREC, bool ACC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FP_XWAVES_ACC(PREC, RECON, Y, ACC),
                                                                      FP_XWAVES_ACC(PREC, RECON, Y, ACC))))
-void k_sweep_x(GeoK G, SchemeK sk, const double* __restrict__ met, const double* qs, EpiK ep) {
+void k_sweep_x(GeoK G, SchemeK sk, const double* __restrict__ met, const double* qs, EpiK ep, XPos step,
+               unsigned items) {
     constexpr int NE = x_entries(PREC, RECON, Y);
     __shared__ XLds<DIM, NE> lds[4];
     XLds<DIM, NE>& L = lds[wave_id()];
-    const unsigned total = ((unsigned)G.n[0] + 1) * (unsigned)G.n[1] * (unsigned)G.n[2];
-    const unsigned j = (unsigned)xcd_block(blockIdx.x, gridDim.x) * 4 + wave_id();
-    const unsigned W1 = (unsigned)G.xw - 1;
-    // items of W faces start W - 1 apart; the last face starts none
-    if ((unsigned long)j * W1 >= total - 1) return;
+    const unsigned b = blockIdx.x, nb = gridDim.x, x = b % 8;
+    const unsigned j = nb % 8 ? (unsigned)xcd_block(b, nb) * 4 + wave_id() : items * x / 8 + b / 8 * 4 + wave_id();
+    const unsigned end = nb % 8 ? items : items * (x + 1) / 8;
+    if (j >= end) return;
+    const unsigned W1 = (unsigned)G.xw - 1, lim = end * W1;  // items of W faces start W - 1 apart
     XPos pos = x_pos(G, j * W1);
-    const XPos step = x_pos(G, gridDim.x * 4 * W1);
     XItem it = x_item<NE>(G, pos);
     x_stage<DIM, NE>(G, met, qs, it, L.b[0]);
     __builtin_amdgcn_s_waitcnt(0);
@@ -667,7 +673,7 @@ void k_sweep_x(GeoK G, SchemeK sk, const double* __restrict__ met, const double*
     for (int cur = 0;; cur ^= 1) {
         XItem next = it;
         x_advance(G, step, pos);
-        const bool more = pos.F0 < total - 1;
+        const bool more = pos.F0 < lim;
         if (more) {
             next = x_item<NE>(G, pos);
             x_stage<DIM, NE>(G, met, qs, next, L.b[cur ^ 1]);
