@@ -950,7 +950,7 @@ __global__ __launch_bounds__(256) FP_SWEEP_ATTR void k_sweep_wg(GeoK G, SchemeK 
 // epilogue, so the residual accumulator stays in registers.
 // Why: on a block of a few thousand nodes a launch lasts as long as one
 // chain of load, face and store, whatever its size, and this runs the two
-// directions side by side: 7.3 us per RK stage of a 64^2 WENO5 block, launch
+// directions side by side: 7.5 us per RK stage of a 64^2 WENO5 block, launch
 // gap included, against 13.9 for the two sweeps (and 10.2 for a workgroup
 // that marches along j over a ring of rows, which was tried first).  It
 // evaluates every eta face twice, so it pays while the chip has room.  The
